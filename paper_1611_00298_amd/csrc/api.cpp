@@ -75,9 +75,8 @@ hipError_t launch_lanczos_axpy(void* w, const void* v, const void* vp, double al
 int action_blocks(int V);
 hipError_t launch_eofa_action(const void* phi, const void* chiL, const void* chiR, const double* om,
                               double k, void* Mphi, double* partial, int V, int Ls, hipStream_t st);
-hipError_t launch_force(const void* U, const void* chiLe, const void* chiLo, const void* chiRe,
-                        const void* chiRo, const int* nbr, const int* sites, double k, void* F, void* G,
-                        const int L[4], int Ls, int aperiodic, int NS, int nblk, size_t N, hipStream_t st);
+hipError_t launch_force(const void* U, const void* chiL, const void* chiR, double k, void* F, void* G,
+                        const int L[4], int Ls, int aperiodic, hipStream_t st);
 int md_blocks(int nlink);
 hipError_t md_scratch_address(double** out);
 hipError_t launch_md_update(void* U, void* P, const void* F, double dt_p, double dt_u, int nlink,
@@ -167,7 +166,7 @@ struct eofa_ctx {
     int* sites[4] = {nullptr, nullptr, nullptr, nullptr};   // hop traversal (site per slot) per precision
     int blk[4] = {0, 0, 0, 0};   // the table lists whole 2x2x2x2 blocks (FP32 and matrix-core paths)
     int* nbrb[4] = {nullptr, nullptr, nullptr, nullptr};   // block-major neighbours of a block table
-    int* fsites = nullptr;   // the per-site FP64 traversal (force kernel, dense hops)
+    int* fsites = nullptr;   // the per-site FP64 traversal (dense hops)
     void* lnkb[4] = {nullptr, nullptr, nullptr, nullptr};  // block-major links of a block table (P32, P16, PB16)
     void* gauge[4] = {nullptr, nullptr, nullptr, nullptr};
     void* U_nat = nullptr;
@@ -1881,11 +1880,11 @@ int eofa_ctx_create(eofa_ctx_t** out, const eofa_geom_t* g, const void* U, void*
                 }
                 const std::vector<int> ord = site_order(c, default_tiling(c, p, blocks), blocks);
                 c->blk[p] = blocks;
-                if (p == P64) {   // the force kernel and the dense hops keep the per-site order (faster for them)
+                if (p == P64) {   // the dense hops keep the per-site order (faster for them)
                     const std::vector<int> fo = blocks ? site_order(c, default_tiling(c, P64, false), false) : ord;
-                    hipchk(hipMalloc((void**)&c->fsites, sizeof(int) * fo.size()), "hipMalloc(force table)");
+                    hipchk(hipMalloc((void**)&c->fsites, sizeof(int) * fo.size()), "hipMalloc(per-site table)");
                     hipchk(hipMemcpy(c->fsites, fo.data(), sizeof(int) * fo.size(), hipMemcpyHostToDevice),
-                           "copy force table");
+                           "copy per-site table");
                 }
                 if (blocks) {
                     const std::vector<int> nbb = block_neighbours(c, ord);
@@ -2046,16 +2045,8 @@ int eofa_force(eofa_ctx_t* c, double m1, double m2, const void* phi, const void*
             chiL = cl;
             chiR = cr;
         }
-        // chi into the FP64 device layout, then one work-item per 5D site
-        Half& le = ws(c, "force_chiL_e", P64);
-        Half& lo = ws(c, "force_chiL_o", P64);
-        Half& re = ws(c, "force_chiR_e", P64);
-        Half& ro = ws(c, "force_chiR_o", P64);
-        hipchk(launch_nat5_to_dev(chiL, le.d, lo.d, c->L, c->Ls, c->N, c->st), "layout");
-        hipchk(launch_nat5_to_dev(chiR, re.d, ro.d, c->L, c->Ls, c->N, c->st), "layout");
         const int ev = timing_begin(c);
-        hipchk(launch_force(c->U_nat, le.d, lo.d, re.d, ro.d, c->nbr, c->fsites, k, F, G, c->L, c->Ls,
-                            c->aperiodic, c->NS, c->nblk_hop, c->N, c->st), "force");
+        hipchk(launch_force(c->U_nat, chiL, chiR, k, F, G, c->L, c->Ls, c->aperiodic, c->st), "force");
         // algorithmic bytes: chi_L and chi_R once, U, F (and G)
         timing_end(c, ev, C_FORCE, 2.0 * c->V * c->Ls * 192.0 + 4.0 * c->V * 144.0 * (G ? 3.0 : 2.0));
         hipchk(hipStreamSynchronize(c->st), "hipStreamSynchronize");

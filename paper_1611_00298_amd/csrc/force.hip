@@ -9,7 +9,7 @@
 // boundary sign of the link.  Because (1+gamma_mu) has rank two,
 // B = sum_{s} sum_{j=0,1} h_j (x) g_j^dag with h = chi_up + A_mu chi_lo at x
 // and g = chi_up - A_mu chi_lo at (x+mu, Ls-1-s) (the minus sign is gamma_5).
-// FP64 throughout; one work-item per 5D site, fields in the FP64 device layout.
+// FP64 throughout; one work-item per link, chi in the natural layout.
 #include "internal.h"
 
 namespace eofa {
@@ -66,107 +66,177 @@ __device__ __forceinline__ void force_from_B(const cplx (&B)[9], const double2* 
     }
 }
 
-// Work-item (site, s) of parity p, workgroups of NS whole sites
-// x Ls slices in the per-site FP64 traversal (site table, XCD ranges).
-// chi_L, chi_R in the FP64 device layout (block c of 5D site n at
-// base[c N + n], n = cb Ls + s).  For each system and direction mu every
-// work-item forms its slice's term of
-// B_mu(x) = sum_{s, j} h_j(x, s) (x) g_j(x+mu, Ls-1-s)^dag; the Ls terms of a
-// site are summed in LDS in a fixed order (chi_R's sums subtracted from
-// chi_L's), and 4 NS work-items then finish the links of the workgroup's sites.
-__global__ void __launch_bounds__(256, 3) k_force_dev(const double2* __restrict__ chiLe,
-                                                   const double2* __restrict__ chiLo,
-                                                   const double2* __restrict__ chiRe,
-                                                   const double2* __restrict__ chiRo,
-                                                   const double2* __restrict__ U, const int* __restrict__ nbr,
-                                                   const int* __restrict__ sites, double k,
-                                                   double2* __restrict__ F, double2* __restrict__ G, Geo g,
-                                                   int NS, size_t N) {
-    extern __shared__ double red[];   // [NT][19] slice terms, then [4][NS][18] sums
-    const int NT = blockDim.x, tid = threadIdx.x, Ls = g.Ls;
-    const int sl = tid / Ls, s = tid - sl * Ls;
-    // the two parities of a slot range run back to back on one XCD, so the
-    // spinors one reads as neighbours are still in L2 when the other reads
-    // them as its own sites
-    const int lbp = xcd_block(gridDim.x);
-    const int p = lbp & 1, lb = lbp >> 1;
-    const int slot = lb * NS + sl;
-    const int cb = sites ? sites[slot] : slot;
-    const bool active = cb < g.Vh;
-    const double2* ownL = p ? chiLo : chiLe;
-    const double2* othL = p ? chiLe : chiLo;
-    const double2* ownR = p ? chiRo : chiRe;
-    const double2* othR = p ? chiRe : chiRo;
-    double* sums = red + (size_t)NT * 19;
-    const size_t na = (size_t)cb * Ls + s;
-    // the forward neighbours' indices, loaded once and before any gather
-    int nbf[4];
+// A workgroup owns a 4D tile of 64 sites (two extents of 4 and two of 2) and
+// all four directions: wavefront mu takes direction mu, its lanes the sites,
+// so the sum over s stays in each work-item's registers.  chi is read in the
+// natural layout, where a 4D site's spinor of one slice is 192 contiguous
+// bytes.  Per step the workgroup stages two slices, s and Ls-1-s, of the
+// tile and its four forward faces in LDS and forms both products of the pair
+// (own slice s with the neighbours' Ls-1-s, and the other way round).
+// A slice pair costs 2.5 spinor reads per site (own and faces) where a gather
+// per direction costs 5, and the next step's words are in registers while a
+// step computes.  Bound by memory: at 24^3x64, Ls = 24 it takes 3.10 ms for
+// 8.7 GB of operands (about 1.5 times that from beyond L2); a per-5D-site
+// gather in the device layout took 4.10 ms after two layout passes of 1.98 ms.
+// At 16^3x32, Ls = 16 with G: 0.33 ms against 0.86 ms.
+// Slots: 64 own sites, then the faces x+mu of the four directions; a slot
+// beyond the lattice (ragged tiles) holds the site it wraps to.
+constexpr int FT_SITES = 64;
+constexpr int FT_SLOTS = FT_SITES + 16 + 16 + 32 + 32;
+constexpr int FT_STR = FT_SLOTS + 1;            // odd: the records' 12 words spread over the banks
+constexpr int FT_CHUNKS = FT_SLOTS * 12;        // 16-byte words of one staged slice
+constexpr int FT_LOADS = (FT_CHUNKS + 255) / 256;
+
+typedef double d2v __attribute__((ext_vector_type(2)));
+
+struct ForceTile {
+    int lg[4];   // log2 of the tile extents (1 or 2)
+    int n[4];    // tiles along each direction
+};
+
+// acc += sum_j h_j (x) g_j^dag, h_j of the spinor at p and g_j of the one at q
+template <int MU>
+__device__ __forceinline__ void force_pair(const d2v* __restrict__ p, const d2v* __restrict__ q,
+                                           cplx (&acc)[9]) {
+    cplx h[2][3], gg[2][3];
 #pragma unroll
-    for (int mu = 0; mu < 4; ++mu) nbf[mu] = active ? nbr[((size_t)p * 8 + mu) * g.Vh + cb] : 0;
-    // chi_L then chi_R: the work-item's own spinor is loaded once per system
-    // and kept in registers over the four directions
-#pragma unroll 1
-    for (int sys = 0; sys < 2; ++sys) {
-        const double2* a = sys ? ownR : ownL;
-        const double2* b = sys ? othR : othL;
-        double2 own[12];
-        for (int q = 0; q < 12; ++q) own[q] = active ? a[q * N + na] : make_double2(0.0, 0.0);
-#pragma unroll 1
-        for (int mu = 0; mu < 4; ++mu) {
-            cplx acc[9];
-            for (int q = 0; q < 9; ++q) acc[q] = {0.0, 0.0};
-            if (active) {
-                const size_t nn = (size_t)nbf[mu] * Ls + (Ls - 1 - s);
-                cplx h[2][3], gg[2][3];
-                for (int cc = 0; cc < 3; ++cc) {
-                    const double2 b0 = b[cc * N + nn], b1 = b[(3 + cc) * N + nn];
-                    const double2 b2 = b[(6 + cc) * N + nn], b3 = b[(9 + cc) * N + nn];
-                    cplx p0, p1, q0, q1;
-                    amul(mu, {own[6 + cc].x, own[6 + cc].y}, {own[9 + cc].x, own[9 + cc].y}, p0, p1);
-                    amul(mu, {b2.x, b2.y}, {b3.x, b3.y}, q0, q1);
-                    h[0][cc] = {own[cc].x + p0.r, own[cc].y + p0.i};
-                    h[1][cc] = {own[3 + cc].x + p1.r, own[3 + cc].y + p1.i};
-                    gg[0][cc] = {b0.x - q0.r, b0.y - q0.i};
-                    gg[1][cc] = {b1.x - q1.r, b1.y - q1.i};
-                }
-                for (int j = 0; j < 2; ++j)
-                    for (int x = 0; x < 3; ++x)
-                        for (int y = 0; y < 3; ++y) {
-                            const cplx t = cmulc(h[j][x], gg[j][y]);
-                            acc[3 * x + y].r += t.r;
-                            acc[3 * x + y].i += t.i;
-                        }
+    for (int cc = 0; cc < 3; ++cc) {
+        const d2v a0 = p[cc * FT_STR], a1 = p[(3 + cc) * FT_STR];
+        const d2v a2 = p[(6 + cc) * FT_STR], a3 = p[(9 + cc) * FT_STR];
+        const d2v b0 = q[cc * FT_STR], b1 = q[(3 + cc) * FT_STR];
+        const d2v b2 = q[(6 + cc) * FT_STR], b3 = q[(9 + cc) * FT_STR];
+        cplx p0, p1, q0, q1;
+        amul(MU, {a2.x, a2.y}, {a3.x, a3.y}, p0, p1);
+        amul(MU, {b2.x, b2.y}, {b3.x, b3.y}, q0, q1);
+        h[0][cc] = {a0.x + p0.r, a0.y + p0.i};
+        h[1][cc] = {a1.x + p1.r, a1.y + p1.i};
+        gg[0][cc] = {b0.x - q0.r, b0.y - q0.i};
+        gg[1][cc] = {b1.x - q1.r, b1.y - q1.i};
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int x = 0; x < 3; ++x)
+#pragma unroll
+            for (int y = 0; y < 3; ++y) {
+                const cplx u = h[j][x], v = gg[j][y];
+                cplx& o = acc[3 * x + y];
+                o.r = fmadd(u.r, v.r, fmadd(u.i, v.i, o.r));
+                o.i = fmadd(u.i, v.r, fmadd(-u.r, v.i, o.i));
             }
-            for (int q = 0; q < 9; ++q) {
-                red[tid * 19 + 2 * q] = acc[q].r;
-                red[tid * 19 + 2 * q + 1] = acc[q].i;
-            }
-            __syncthreads();
-            // sum over s in a fixed order into sums[mu][site][18]: chi_L minus chi_R
-            for (int t = tid; t < NS * 18; t += NT) {
-                const int j = t / 18, q = t - 18 * j;
-                double v = 0;
-                for (int u = 0; u < Ls; ++u) v += red[(j * Ls + u) * 19 + q];
-                double* dst = sums + mu * NS * 18 + t;
-                *dst = sys ? *dst - v : v;
-            }
-            __syncthreads();
+}
+
+__global__ void __launch_bounds__(256, 2) k_force(const double2* __restrict__ chiL, const double2* __restrict__ chiR,
+                                                  const double2* __restrict__ U, double k, double2* __restrict__ F,
+                                                  double2* __restrict__ G, Geo g, ForceTile ft) {
+    __shared__ d2v tile[2][12 * FT_STR];
+    __shared__ int nat[FT_SLOTS];   // natural site index of each slot
+    const int tid = threadIdx.x, mu = tid >> 6, lane = tid & 63;
+    int o[4];   // tile origin
+    {
+        int r = xcd_block(gridDim.x);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            o[d] = (r % ft.n[d]) << ft.lg[d];
+            r /= ft.n[d];
         }
     }
-    // one work-item per (site, mu) finishes the links
-    for (int t = tid; t < 4 * NS; t += NT) {
-        const int mu = t / NS, j = t - mu * NS;
-        const int slot2 = lb * NS + j;
-        const int cb2 = sites ? sites[slot2] : slot2;
-        if (cb2 >= g.Vh) continue;
-        int c[4];
-        const int i = natural_site(g, p, cb2, c);
-        const double sigma = (mu == 3 && g.aperiodic && c[3] == g.L[3] - 1) ? -1.0 : 1.0;
-        cplx B[9];
-        const double* bs = sums + (mu * NS + j) * 18;
-        for (int q = 0; q < 9; ++q) B[q] = {bs[2 * q], bs[2 * q + 1]};
-        const size_t l = ((size_t)mu * g.V + i) * 9;
-        force_from_B(B, U + l, sigma, k, F + l, G ? G + l : nullptr);
+    // first slot of each face
+    int face[4];
+    face[0] = FT_SITES;
+#pragma unroll
+    for (int d = 1; d < 4; ++d) face[d] = face[d - 1] + (FT_SITES >> ft.lg[d - 1]);
+    if (tid < FT_SLOTS) {
+        int fd = -1, r = tid;   // face direction (-1: own site) and index within it
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+            if (tid >= face[d]) { fd = d; r = tid - face[d]; }
+        int i = 0, stride = 1;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            int c = 1 << ft.lg[d];
+            if (d != fd) { c = r & (c - 1); r >>= ft.lg[d]; }
+            i += ((o[d] + c) % g.L[d]) * stride;
+            stride *= g.L[d];
+        }
+        nat[tid] = i;
+    }
+    // this lane's site, and the slot of its neighbour along mu
+    int own[4], r = lane, nb = 0, sh = 0;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        own[d] = r & ((1 << ft.lg[d]) - 1);
+        r >>= ft.lg[d];
+    }
+    bool inside = true, active = true;
+    int step = 1;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        if (d == mu) inside = own[d] + 1 < (1 << ft.lg[d]);
+        else { nb |= own[d] << sh; sh += ft.lg[d]; }
+        if (d < mu) step <<= ft.lg[d];
+        active = active && o[d] + own[d] < g.L[d];
+    }
+    nb = inside ? lane + step : nb + (mu == 0 ? face[0] : mu == 1 ? face[1] : mu == 2 ? face[2] : face[3]);
+    __syncthreads();
+    // staging: word c of slot j by work-item (12 j + c) mod 256; the work-items past the end repeat the last word
+    uint32_t src[FT_LOADS];
+    int dst[FT_LOADS];
+#pragma unroll
+    for (int u = 0; u < FT_LOADS; ++u) {
+        const int e = min(tid + 256 * u, FT_CHUNKS - 1), j = e / 12, c = e - 12 * j;
+        src[u] = (uint32_t)nat[j] * 12u + (uint32_t)c;
+        dst[u] = c * FT_STR + j;
+    }
+    const int Ls = g.Ls, half = (Ls + 1) / 2;
+    const size_t slice = (size_t)g.V * 12;
+    d2v va[FT_LOADS], vb[FT_LOADS];
+    auto fetch = [&](int it) __attribute__((always_inline)) {   // step it: system it / half, slices q and Ls-1-q
+        const double2* chi = it < half ? chiL : chiR;
+        const int q = it < half ? it : it - half;
+        const d2v* a = reinterpret_cast<const d2v*>(chi + (size_t)q * slice);
+        const d2v* b = reinterpret_cast<const d2v*>(chi + (size_t)(Ls - 1 - q) * slice);
+#pragma unroll
+        for (int u = 0; u < FT_LOADS; ++u) va[u] = a[src[u]];
+#pragma unroll
+        for (int u = 0; u < FT_LOADS; ++u) vb[u] = b[src[u]];
+    };
+    cplx acc[9];
+#pragma unroll
+    for (int q = 0; q < 9; ++q) acc[q] = {0.0, 0.0};
+    fetch(0);
+#pragma unroll 1
+    for (int it = 0; it < 2 * half; ++it) {
+        __syncthreads();   // the previous step's slices are read
+#pragma unroll
+        for (int u = 0; u < FT_LOADS; ++u) {
+            tile[0][dst[u]] = va[u];
+            tile[1][dst[u]] = vb[u];
+        }
+        __syncthreads();
+        if (it + 1 < 2 * half) fetch(it + 1);   // in flight while this step computes
+        const int q = it < half ? it : it - half;
+        const int n = 2 * q + 1 == Ls ? 1 : 2;   // the middle slice of an odd Ls pairs with itself
+#pragma unroll 1
+        for (int t = 0; t < n; ++t) {
+            const d2v* p = tile[t] + lane;
+            const d2v* w = tile[1 - t] + nb;
+            switch (mu) {
+            case 0: force_pair<0>(p, w, acc); break;
+            case 1: force_pair<1>(p, w, acc); break;
+            case 2: force_pair<2>(p, w, acc); break;
+            default: force_pair<3>(p, w, acc); break;
+            }
+        }
+        if (it == half - 1) {   // chi_R enters with the opposite sign: acc = -B[chi_L] + B[chi_R] from here
+#pragma unroll
+            for (int e = 0; e < 9; ++e) acc[e] = {-acc[e].r, -acc[e].i};
+        }
+    }
+    if (active) {
+        const double sigma = (mu == 3 && g.aperiodic && o[3] + own[3] == g.L[3] - 1) ? -1.0 : 1.0;
+        const size_t l = ((size_t)mu * g.V + nat[lane]) * 9;
+        force_from_B(acc, U + l, -sigma, k, F + l, G ? G + l : nullptr);
     }
 }
 
@@ -245,20 +315,35 @@ __global__ void __launch_bounds__(256) k_md_update(double2* __restrict__ U, doub
     }
 }
 
-hipError_t launch_force(const void* U, const void* chiLe, const void* chiLo, const void* chiRe,
-                        const void* chiRo, const int* nbr, const int* sites, double k, void* F, void* G,
-                        const int L[4], int Ls, int aperiodic, int NS, int nblk, size_t N, hipStream_t st) {
+// The tile: extents of 4 along two directions and 2 along the other two, the
+// pair that pads the lattice least.  Ties go to z and t: tiles are walked x
+// first, so the workgroups of an XCD that run together cover x and y and
+// share those faces in its L2, while the z and t faces, halved by the longer
+// extents, come from beyond it (24^3x64, Ls = 24: 3.10 ms against 3.37 ms
+// with the long extents along x and y).
+hipError_t launch_force(const void* U, const void* chiL, const void* chiR, double k, void* F, void* G,
+                        const int L[4], int Ls, int aperiodic, hipStream_t st) {
     Geo g;
     for (int mu = 0; mu < 4; ++mu) g.L[mu] = L[mu];
     g.V = L[0] * L[1] * L[2] * L[3];
     g.Vh = g.V / 2;
     g.Ls = Ls;
     g.aperiodic = aperiodic;
-    const int NT = NS * Ls;
-    const size_t shm = sizeof(double) * ((size_t)NT * 19 + (size_t)4 * NS * 18);
-    hipLaunchKernelGGL(k_force_dev, dim3(2 * nblk), dim3(NT), shm, st, (const double2*)chiLe,
-                       (const double2*)chiLo, (const double2*)chiRe, (const double2*)chiRo, (const double2*)U,
-                       nbr, sites, k, (double2*)F, (double2*)G, g, NS, N);
+    ForceTile ft{};
+    long best = 0;
+    for (int a = 0; a < 3; ++a)
+        for (int b = a + 1; b < 4; ++b) {
+            ForceTile c;
+            long tiles = 1;
+            for (int d = 0; d < 4; ++d) {
+                c.lg[d] = d == a || d == b ? 2 : 1;
+                c.n[d] = (L[d] + (1 << c.lg[d]) - 1) >> c.lg[d];
+                tiles *= c.n[d];
+            }
+            if (best == 0 || tiles <= best) { best = tiles; ft = c; }
+        }
+    hipLaunchKernelGGL(k_force, dim3((unsigned)best), dim3(256), 0, st, (const double2*)chiL, (const double2*)chiR,
+                       (const double2*)U, k, (double2*)F, (double2*)G, g, ft);
     return hipGetLastError();
 }
 
