@@ -53,10 +53,10 @@ hipError_t launch_gauge_convert(int po, const void* in, void* out, size_t n, hip
 hipError_t launch_gauge_c16(const void* in, void* out, int Vh, int bf, hipStream_t st);
 hipError_t launch_links_blocked(const void* src, void* dst, const int* sites, int Vh, int nslot, int wide,
                                 hipStream_t st);
-hipError_t launch_nat5_to_dev(const void* nat, void* de, void* dodd, const int L[4], int Ls, size_t N,
-                              hipStream_t st);
-hipError_t launch_dev_to_nat5(void* nat, const void* de, const void* dodd, const int L[4], int Ls,
-                              size_t N, hipStream_t st);
+hipError_t launch_nat_to_dev(int prec, const void* nat, void* e, float* en, void* o, float* on, int par, const Op5& B,
+                             double mp, double mm, const int L[4], int Ls, size_t N, hipStream_t st);
+hipError_t launch_dev_to_nat(int prec, void* nat, void* e, float* en, void* o, float* on, const int L[4], int Ls,
+                             size_t N, hipStream_t st);
 hipError_t launch_eofa_source(const void* phi, const double* om, void* bLe, void* bLo, void* bRe,
                               void* bRo, const int L[4], int Ls, size_t N, hipStream_t st);
 hipError_t launch_hb_init(const void* eta, void* phi, double c0, size_t n, hipStream_t st);
@@ -313,6 +313,10 @@ struct HopCall {
     int s_num = 0, s_den = 0, s_alpha = -1;
     // dense blocks [D5+, D5-, D5inv+, D5inv-] (the dense D_EOFA path, any of its precisions)
     const double* dmat = nullptr;
+    // FP64 with natural-layout aux and output (dwf_apply); zero_pair: zeros to the other parity's sites
+    const void* aux_nat = nullptr;
+    void* out_nat = nullptr;
+    bool zero_pair = false;
 };
 
 void run_hop(eofa_ctx* c, const HopCall& h) {
@@ -327,8 +331,16 @@ void run_hop(eofa_ctx* c, const HopCall& h) {
     memset(&a, 0, sizeof(a));
     a.in = h.in ? h.in->d : nullptr;
     a.in_nrm = h.in ? h.in->nrm : nullptr;
-    a.out = h.out->d;
-    a.out_nrm = h.out->nrm;
+    if ((h.out_nat != nullptr) != (h.aux_nat != nullptr) || (h.out_nat != nullptr) == (h.out != nullptr) ||
+        (h.out_nat && (h.prec != P64 || !h.hop || h.aux || h.aux2 || h.B.kind != 1 || h.B2.kind != 0 || h.C.kind != 0 ||
+                       h.partial || h.dev_alpha || h.dmat)))
+        fail(EOFA_EDEVICE, "internal: unsupported natural-layout hop form");
+    a.aux_nat = h.aux_nat;
+    a.out_nat = h.out_nat;
+    a.zero_pair = h.zero_pair;
+    for (int mu = 0; mu < 4; ++mu) a.L[mu] = c->L[mu];
+    a.out = h.out ? h.out->d : nullptr;
+    a.out_nrm = h.out ? h.out->nrm : nullptr;
     a.aux = h.aux ? h.aux->d : nullptr;
     a.aux_nrm = h.aux ? h.aux->nrm : nullptr;
     a.aux2 = h.aux2 ? h.aux2->d : nullptr;
@@ -384,7 +396,8 @@ void run_hop(eofa_ctx* c, const HopCall& h) {
     // bookkeeping: flops (fixed convention) and algorithmic bytes
     double f = 0, nfields = 1;
     if (h.hop) f += 1320.0 + op_flops(h.A, c->Ls), nfields += 1;
-    if (h.aux) f += op_flops(h.B, c->Ls) + op_flops(h.B2, c->Ls) + (h.hop ? 24.0 : 0.0), nfields += 1;
+    if (h.aux || h.aux_nat)
+        f += op_flops(h.B, c->Ls) + op_flops(h.B2, c->Ls) + (h.hop ? 24.0 : 0.0), nfields += h.zero_pair ? 2 : 1;
     if (h.aux2) f += 24.0, nfields += 1;
     f += op_flops(h.C, c->Ls);
     c->flops += f * (double)c->n5;
@@ -457,6 +470,21 @@ void convert(eofa_ctx* c, const Half& in, Half& out) {
     hipchk(launch_convert(in.prec, out.prec, in.d, in.nrm, out.d, out.nrm, c->n5, c->N, c->nblk_blas, c->st),
            "convert");
     timing_end(c, ev, C_BLAS, (double)c->n5 * (spinor_bytes(in.prec) + spinor_bytes(out.prec)));
+}
+
+// natural-layout complex128 5D field -> half fields of one precision (e or o NULL: that parity is
+// left out), optionally B(nat) in FP64; and back (e NULL: zeros)
+void from_natural(eofa_ctx* c, const void* nat, const Half* e, const Half* o, Op5 B = I5, double mp = 0,
+                  double mm = 0) {
+    const Half& h = e ? *e : *o;
+    hipchk(launch_nat_to_dev(h.prec, nat, e ? e->d : nullptr, e ? e->nrm : nullptr, o ? o->d : nullptr,
+                             o ? o->nrm : nullptr, e && o ? -1 : o ? 1 : 0, B, mp, mm, c->L, c->Ls, c->N, c->st),
+           "layout");
+}
+
+void to_natural(eofa_ctx* c, const Half* e, const Half* o, void* nat) {
+    hipchk(launch_dev_to_nat(o->prec, nat, e ? e->d : nullptr, e ? e->nrm : nullptr, o->d, o->nrm, c->L, c->Ls, c->N,
+                             c->st), "layout");
 }
 
 void zero(eofa_ctx* c, Half& f) {
@@ -1207,7 +1235,7 @@ int solve_dense_impl(eofa_ctx* c, double m1, double m2, const void* phi, void* c
                "hipMemcpy(dense blocks)");
         hipchk(hipStreamSynchronize(c->st), "hipStreamSynchronize");
         const DenseOut o = solve_dense(c, dm, sys ? bRe : bLe, sys ? bRo : bLo, ce, co, *sp);
-        hipchk(launch_dev_to_nat5(sys ? chiR : chiL, ce.d, co.d, c->L, c->Ls, c->N, c->st), "layout");
+        to_natural(c, &ce, &co, sys ? chiR : chiL);
         if (stats) {
             stats->iters[sys] = o.iters;
             stats->reliable_updates[sys] = o.reliable;
@@ -1270,7 +1298,7 @@ int solve_impl(eofa_ctx* c, double m1, double m2, const void* phi, const void* x
         const double mp = m1, mm = sys == 0 ? m1 : m2;
         const void* x0 = sys == 0 ? x0L : x0R;
         if (x0) {   // y0 = Dtilde^-1 chi0
-            hipchk(launch_nat5_to_dev(x0, ce.d, co.d, c->L, c->Ls, c->N, c->st), "layout");
+            from_natural(c, x0, &ce, &co);
             local_op(c, P64, ce, ye, I5, DtInv(c, 0), mp, mm);
             local_op(c, P64, co, yo, I5, DtInv(c, 0), mp, mm);
         }
@@ -1294,7 +1322,7 @@ int solve_impl(eofa_ctx* c, double m1, double m2, const void* phi, const void* x
             c->chrono_m[sys][0] = mp;
             c->chrono_m[sys][1] = mm;
         }
-        hipchk(launch_dev_to_nat5(sys ? chiR : chiL, ce.d, co.d, c->L, c->Ls, c->N, c->st), "layout");
+        to_natural(c, &ce, &co, sys ? chiR : chiL);
         if (stats) {
             stats->iters[sys] = o.iters;
             stats->reliable_updates[sys] = o.reliable;
@@ -1930,37 +1958,57 @@ int dwf_apply(eofa_ctx_t* c, double mp, double mm, int dagger, int eo, eofa_prec
         if (eo != 0 && eo != 1) fail(EOFA_EINVAL, "eo must be 0 or 1");
         if (in == out) fail(EOFA_EINVAL, "in and out may not alias");
         const int P = prec;
-        Half& ie = ws(c, "ap_in_e", P64);
-        Half& io = ws(c, "ap_in_o", P64);
-        Half& oe = ws(c, "ap_out_e", P64);
-        Half& oo = ws(c, "ap_out_o", P64);
-        hipchk(launch_nat5_to_dev(in, ie.d, io.d, c->L, c->Ls, c->N, c->st), "layout");
-        Half* pie = &ie; Half* pio = &io; Half* poe = &oe; Half* poo = &oo;
-        if (P != P64) {
-            pie = &ws(c, "ap_in_e", P); pio = &ws(c, "ap_in_o", P);
-            poe = &ws(c, "ap_out_e", P); poo = &ws(c, "ap_out_o", P);
-            convert(c, ie, *pie);
-            convert(c, io, *pio);
+        if (P == P64) {
+            // FP64: the hop's input goes to the device layout (already Dtilde in
+            // where the hop needs that); the hop that ends the operator reads
+            // the diagonal term's operand from `in` and writes `out` itself
+            auto final_hop = [&](const Half& x, int par, double ch) {
+                HopCall h;
+                h.prec = P; h.dag = dagger != 0; h.par = par; h.mp = mp; h.mm = mm;
+                h.in = &x; h.ch = ch; h.ca = 1.0;
+                h.A = dagger ? Dt(c, 1) : I5;
+                h.B = Mee(c, dagger ? 1 : 0);
+                h.aux_nat = in; h.out_nat = out; h.zero_pair = eo != 0;
+                run_hop(c, h);
+            };
+            const Op5 pre = dagger ? I5 : Dt(c, 0);
+            Half& to = ws(c, "ap_t_o", P);
+            Half& te = ws(c, "ap_t_e", P);
+            from_natural(c, in, eo ? nullptr : &te, &to, pre, mp, mm);
+            if (eo == 0) {
+                final_hop(to, 0, 1.0);   // out_p = M_ee in_p + Dh (Dtilde in)_pbar, or its adjoint
+                final_hop(te, 1, 1.0);
+            } else {
+                if (dagger) schur_k3(c, P, to, te, mp, mm);
+                else schur_k1(c, P, to, te, mp, mm);
+                final_hop(te, 1, -1.0);
+            }
+            return EOFA_OK;
         }
+        Half& pie = ws(c, "ap_in_e", P);
+        Half& pio = ws(c, "ap_in_o", P);
+        Half& poe = ws(c, "ap_out_e", P);
+        Half& poo = ws(c, "ap_out_o", P);
+        from_natural(c, in, eo ? nullptr : &pie, &pio);
         Half& te = ws(c, "ap_t_e", P);
         Half& to = ws(c, "ap_t_o", P);
         if (eo == 0) {
             for (int par = 0; par < 2; ++par) {
                 HopCall h;
                 h.prec = P; h.par = par; h.mp = mp; h.mm = mm;
-                h.out = par ? poo : poe;
-                h.aux = par ? pio : pie;
+                h.out = par ? &poo : &poe;
+                h.aux = par ? &pio : &pie;
                 h.ca = 1.0; h.ch = 1.0;
                 if (!dagger) {
                     // out_p = M_ee in_p + Dh (Dtilde in)_pbar
                     Half& t = par ? te : to;
-                    local_op(c, P, par ? *pie : *pio, t, Dt(c, 0), I5, mp, mm);
+                    local_op(c, P, par ? pie : pio, t, Dt(c, 0), I5, mp, mm);
                     h.in = &t;
                     h.B = Mee(c, 0);
                 } else {
                     // out_p = M_ee^dag in_p + Dtilde^dag Dh^dag in_pbar
                     h.dag = true;
-                    h.in = par ? pie : pio;
+                    h.in = par ? &pie : &pio;
                     h.A = Dt(c, 1);
                     h.B = Mee(c, 1);
                 }
@@ -1968,20 +2016,15 @@ int dwf_apply(eofa_ctx_t* c, double mp, double mm, int dagger, int eo, eofa_prec
             }
         } else {
             if (!dagger) {
-                local_op(c, P, *pio, to, Dt(c, 0), I5, mp, mm);
+                local_op(c, P, pio, to, Dt(c, 0), I5, mp, mm);
                 schur_k1(c, P, to, te, mp, mm);
-                schur_k2(c, P, te, *pio, *poo, mp, mm, nullptr);
+                schur_k2(c, P, te, pio, poo, mp, mm, nullptr);
             } else {
-                schur_k3(c, P, *pio, te, mp, mm);
-                schur_k4(c, P, te, *pio, *poo, mp, mm, nullptr);
+                schur_k3(c, P, pio, te, mp, mm);
+                schur_k4(c, P, te, pio, poo, mp, mm, nullptr);
             }
-            zero(c, *poe);
         }
-        if (P != P64) {
-            convert(c, *poe, oe);
-            convert(c, *poo, oo);
-        }
-        hipchk(launch_dev_to_nat5(out, oe.d, oo.d, c->L, c->Ls, c->N, c->st), "layout");
+        to_natural(c, eo ? nullptr : &poe, &poo, out);
         return EOFA_OK;
     });
 }

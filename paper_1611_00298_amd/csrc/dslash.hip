@@ -952,8 +952,6 @@ __device__ __forceinline__ void hop_blk_mfma(const HopArgs& a, int lb, unsigned 
 //                  the shift) and the rank-one wrap-around correction
 //                  y_q = z_q - m w^(q+1) z_last / (1 + m w^Ls).
 // ---------------------------------------------------------------------------
-constexpr int STR = 25;
-
 template <typename A>
 __device__ __forceinline__ void put_row(A* T, int tid, const A (&v)[24]) {
     A* r = T + tid * STR;
@@ -1155,7 +1153,11 @@ __device__ __forceinline__ double block_sum(double x, double* red) {
     return t;
 }
 
-template <int P, bool DAG, bool HOP, int MF, bool DENSE = false, bool BLK = false>
+// NAT (FP64 hops that end dwf_apply): the diagonal term's operand is read from
+// the natural layout and the result written to it, through the epilogue's
+// tile.  At 24^3x64, Ls = 24 the hop takes 1.90 ms instead of 1.74 ms plus its
+// share of two layout passes (2.26 ms); dwf_apply 9.55 -> 5.32 ms.
+template <int P, bool DAG, bool HOP, int MF, bool DENSE = false, bool BLK = false, bool NAT = false>
 __global__ void __launch_bounds__(256, (MF == 3 && P == P16 && !DENSE) ? 5 : 3) k_hop(const HopArgs a) {
     using A = typename PT<P>::A;
     // column-sweep load batch: what each variant's register budget allows
@@ -1163,6 +1165,7 @@ __global__ void __launch_bounds__(256, (MF == 3 && P == P16 && !DENSE) ? 5 : 3) 
     extern __shared__ unsigned char smem_raw[];
     A* lds = reinterpret_cast<A*>(smem_raw);
     __shared__ double red[16];
+    __shared__ uint32_t rowoff[NAT ? 256 : 1];   // natural offset of each work-item's row
     const int tid = threadIdx.x;
     const int Ls = a.Ls;
     const int sl = tid / Ls;
@@ -1173,6 +1176,12 @@ __global__ void __launch_bounds__(256, (MF == 3 && P == P16 && !DENSE) ? 5 : 3) 
     const bool active = site < a.Vh;
     const size_t n = (size_t)site * Ls + s;
     const A mp = (A)a.mp, mm = (A)a.mm;
+    if constexpr (NAT) {   // read after the barriers of the hop
+        const Geo g{{a.L[0], a.L[1], a.L[2], a.L[3]}, 2 * a.Vh, a.Vh, Ls, 0};
+        int c[4];
+        rowoff[tid] = active ? ((uint32_t)s * 2u * (uint32_t)a.Vh + (uint32_t)natural_site(g, a.par, site, c)) * 12u
+                             : NO_ROW;
+    }
 
     A v[24];
 #pragma unroll
@@ -1256,7 +1265,18 @@ __global__ void __launch_bounds__(256, (MF == 3 && P == P16 && !DENSE) ? 5 : 3) 
 #pragma unroll
             for (int k = 0; k < 24; ++k) v[k] *= ch;
         }
-        if (a.aux) {
+        if constexpr (NAT) {
+            // + ca B(aux), aux in the natural layout, B bidiagonal
+            nat_rows_load(a.aux_nat, rowoff, a.NS * Ls, lds);
+            __syncthreads();
+            A x[24], bx[24];
+            get_row(lds, tid, x);
+            row_bidiag(lds, tid, s, Ls, x, bx, (A)a.opB.a, (A)a.opB.b, a.opB.tr, mp, mm);
+            const A ca = (A)a.ca;
+#pragma unroll
+            for (int k = 0; k < 24; ++k) v[k] = fmadd(ca, bx[k], v[k]);
+            __syncthreads();
+        } else if (a.aux) {
             A x[24];
             if (active) ld_spinor<P, true>(a.aux, a.aux_nrm, a.N, n, x);
             else {
@@ -1307,6 +1327,12 @@ __global__ void __launch_bounds__(256, (MF == 3 && P == P16 && !DENSE) ? 5 : 3) 
         }
     }
     }   // !DENSE
+    if constexpr (NAT) {
+        put_row(lds, tid, v);
+        __syncthreads();
+        nat_rows_store(a.out_nat, rowoff, a.NS * Ls, lds, a.zero_pair != 0);
+        return;
+    }
     if (active) st_spinor<P, true>(a.out, a.out_nrm, a.N, n, v);
     if (a.partial) {
         double x = 0;
@@ -1385,8 +1411,147 @@ __global__ void __launch_bounds__(256) k_pupdate(const void* z, const float* z_n
 }
 
 // ---------------------------------------------------------------------------
+// Natural complex128 5D fields <-> device half fields.  A workgroup holds the
+// slices of a run of 4D sites (par < 0: pairs of both parities; else one
+// parity's sites) as rows of the LDS tile: its wavefronts read and write whole
+// 192-byte records on the natural side and 16-byte words of consecutive 5D
+// sites on the device side.  Bound by memory: in at 24^3x64, Ls = 24 (FP64,
+// 8.2 GB) 1.55 ms with Dtilde applied on the way (one work-item per record
+// took 1.98 ms without it), out at 24^3x16, Ls = 24 (2.0 GB) 0.38 ms (0.54 ms).
+// ---------------------------------------------------------------------------
+struct NatArgs {
+    Geo g;
+    int par;     // 0 or 1: that parity only; < 0: both
+    int ncb;     // checkerboard sites per workgroup
+    size_t N;
+    void* half[2];      // even, odd device half fields (null in dev -> nat: zeros)
+    float* nrm[2];
+};
+
+// row tid of the workgroup: parity, checkerboard site and slice; its natural offset goes to rowoff
+__device__ __forceinline__ bool nat_row(const NatArgs& a, uint32_t* rowoff, int& p, size_t& n, int& s) {
+    const int tid = threadIdx.x, Ls = a.g.Ls, slot = tid / Ls;
+    s = tid - slot * Ls;
+    const int q = slot / a.ncb, cb = blockIdx.x * a.ncb + (slot - q * a.ncb);
+    p = a.par < 0 ? q : a.par;
+    n = (size_t)cb * Ls + s;
+    const bool active = cb < a.g.Vh;
+    int c[4];
+    rowoff[tid] = active ? ((uint32_t)s * (uint32_t)a.g.V + (uint32_t)natural_site(a.g, p, cb, c)) * 12u : NO_ROW;
+    return active;
+}
+
+// half = B(nat) (B bidiagonal, FP64 only, or the identity)
+template <int P>
+__global__ void __launch_bounds__(256) k_nat_to_dev(const void* __restrict__ nat, const NatArgs a, const Op5 B,
+                                                    double mp, double mm) {
+    using A = typename PT<P>::A;
+    extern __shared__ unsigned char smem_raw[];
+    double* T = reinterpret_cast<double*>(smem_raw);
+    __shared__ uint32_t rowoff[256];
+    const int tid = threadIdx.x;
+    int p, s;
+    size_t n;
+    const bool active = nat_row(a, rowoff, p, n, s);
+    __syncthreads();
+    nat_rows_load(nat, rowoff, blockDim.x, T);
+    __syncthreads();
+    double x[24];
+    get_row(T, tid, x);
+    if constexpr (P == P64) {
+        if (B.kind == 1) {
+            double y[24];
+            row_bidiag(T, tid, s, a.g.Ls, x, y, B.a, B.b, B.tr, mp, mm);
+#pragma unroll
+            for (int k = 0; k < 24; ++k) x[k] = y[k];
+        }
+    }
+    if (!active) return;
+    A v[24];
+#pragma unroll
+    for (int k = 0; k < 24; ++k) v[k] = (A)x[k];
+    st_spinor<P>(a.half[p], a.nrm[p], a.N, n, v);
+}
+
+template <int P>
+__global__ void __launch_bounds__(256) k_dev_to_nat(void* __restrict__ nat, const NatArgs a) {
+    using A = typename PT<P>::A;
+    extern __shared__ unsigned char smem_raw[];
+    double* T = reinterpret_cast<double*>(smem_raw);
+    __shared__ uint32_t rowoff[256];
+    int p, s;
+    size_t n;
+    const bool active = nat_row(a, rowoff, p, n, s);
+    A v[24];
+#pragma unroll
+    for (int k = 0; k < 24; ++k) v[k] = 0;
+    if (active && a.half[p]) ld_spinor<P, true>(a.half[p], a.nrm[p], a.N, n, v);
+    double x[24];
+#pragma unroll
+    for (int k = 0; k < 24; ++k) x[k] = (double)v[k];
+    put_row(T, threadIdx.x, x);
+    __syncthreads();
+    nat_rows_store(nat, rowoff, blockDim.x, T, false);
+}
+
+// ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
+static NatArgs nat_args(const int L[4], int Ls, size_t N, int par, void* e, float* en, void* o, float* on, int& NT,
+                        unsigned& nblk) {
+    NatArgs a{};
+    const int V = L[0] * L[1] * L[2] * L[3];
+    a.g = Geo{{L[0], L[1], L[2], L[3]}, V, V / 2, Ls, 0};
+    a.par = par;
+    a.N = N;
+    a.half[0] = e; a.half[1] = o;
+    a.nrm[0] = en; a.nrm[1] = on;
+    const int np = par < 0 ? 2 : 1;
+    a.ncb = std::max(1, 256 / Ls / np);   // Ls <= 64: at least two sites of both parities fit
+    NT = a.ncb * np * Ls;
+    nblk = (unsigned)((a.g.Vh + a.ncb - 1) / a.ncb);
+    return a;
+}
+
+hipError_t launch_nat_to_dev(int prec, const void* nat, void* e, float* en, void* o, float* on, int par, const Op5& B,
+                             double mp, double mm, const int L[4], int Ls, size_t N, hipStream_t st) {
+    int NT;
+    unsigned nblk;
+    const NatArgs a = nat_args(L, Ls, N, par, e, en, o, on, NT, nblk);
+    if (B.kind != 0 && (prec != P64 || B.kind != 1)) return hipErrorInvalidValue;
+    const size_t shm = (size_t)STR * NT * sizeof(double);
+    switch (prec) {
+#define EOFA_CASE(PP) \
+    case PP: hipLaunchKernelGGL((k_nat_to_dev<PP>), dim3(nblk), dim3(NT), shm, st, nat, a, B, mp, mm); break;
+        EOFA_CASE(P64)
+        EOFA_CASE(P32)
+        EOFA_CASE(P16)
+        EOFA_CASE(PB16)
+#undef EOFA_CASE
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_dev_to_nat(int prec, void* nat, void* e, float* en, void* o, float* on, const int L[4], int Ls,
+                             size_t N, hipStream_t st) {
+    int NT;
+    unsigned nblk;
+    const NatArgs a = nat_args(L, Ls, N, -1, e, en, o, on, NT, nblk);
+    const size_t shm = (size_t)STR * NT * sizeof(double);
+    switch (prec) {
+#define EOFA_CASE(PP) \
+    case PP: hipLaunchKernelGGL((k_dev_to_nat<PP>), dim3(nblk), dim3(NT), shm, st, nat, a); break;
+        EOFA_CASE(P64)
+        EOFA_CASE(P32)
+        EOFA_CASE(P16)
+        EOFA_CASE(PB16)
+#undef EOFA_CASE
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
 template <int P, bool DAG, bool HOP>
 static hipError_t launch_hop_t(const HopArgs& a, int nblk, hipStream_t st) {
     using A = typename PT<P>::A;
@@ -1404,6 +1569,16 @@ static hipError_t launch_hop_t(const HopArgs& a, int nblk, hipStream_t st) {
             if (a.depth >= 4) hipLaunchKernelGGL((k_hop<P, DAG, HOP, 4>), dim3(nblk), dim3(NT), shm, st, a);
             else if (a.depth == 3) hipLaunchKernelGGL((k_hop<P, DAG, HOP, 3>), dim3(nblk), dim3(NT), shm, st, a);
             else hipLaunchKernelGGL((k_hop<P, DAG, HOP, 2>), dim3(nblk), dim3(NT), shm, st, a);
+            return hipGetLastError();
+        }
+    }
+    if constexpr (P == P64 && HOP) {
+        if (a.out_nat) {   // dwf_apply: natural-layout aux and output
+            const size_t links = a.blk ? (size_t)(2 * a.NS + 1) * LinkLds<P, 0>::LB + share_bytes(P, false, NT)
+                                       : stage_bytes(LinkLds<P, 0>::LB, a.NS);
+            const size_t shm = std::max((size_t)STR * NT * sizeof(A), links);
+            if (a.blk) hipLaunchKernelGGL((k_hop<P, DAG, HOP, 0, false, true, true>), dim3(nblk), dim3(NT), shm, st, a);
+            else hipLaunchKernelGGL((k_hop<P, DAG, HOP, 0, false, false, true>), dim3(nblk), dim3(NT), shm, st, a);
             return hipGetLastError();
         }
     }

@@ -66,37 +66,6 @@ __global__ void k_gauge_c16(const double2* __restrict__ in, uint32_t* __restrict
     }
 }
 
-// natural 5D complex128 <-> FP64 device half fields (both parities)
-__global__ void k_nat5_to_dev(const double2* __restrict__ nat, double2* __restrict__ de,
-                              double2* __restrict__ dodd, Geo g, size_t N) {
-    const size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-    const size_t nh = (size_t)g.Vh * g.Ls;
-    if (t >= 2 * nh) return;
-    const int p = (int)(t / nh);
-    const size_t r = t - p * nh;
-    const int cb = (int)(r / g.Ls), s = (int)(r - (size_t)cb * g.Ls);
-    int c[4];
-    const int i = natural_site(g, p, cb, c);
-    const double2* src = nat + ((size_t)s * g.V + i) * 12;
-    double2* dst = p ? dodd : de;
-    for (int k = 0; k < 12; ++k) dst[k * N + r] = src[k];
-}
-
-__global__ void k_dev_to_nat5(double2* __restrict__ nat, const double2* __restrict__ de,
-                              const double2* __restrict__ dodd, Geo g, size_t N) {
-    const size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-    const size_t nh = (size_t)g.Vh * g.Ls;
-    if (t >= 2 * nh) return;
-    const int p = (int)(t / nh);
-    const size_t r = t - p * nh;
-    const int cb = (int)(r / g.Ls), s = (int)(r - (size_t)cb * g.Ls);
-    int c[4];
-    const int i = natural_site(g, p, cb, c);
-    double2* dst = nat + ((size_t)s * g.V + i) * 12;
-    const double2* src = p ? dodd : de;
-    for (int k = 0; k < 12; ++k) dst[k] = src[k * N + r];
-}
-
 // Cayley-form sources of the two EOFA systems (footnote of Section 5.1):
 //   b_L = g5 R5 Omega_- P_- phi : b_L(s) = -Omega_-(Ls-1-s) phi_lower
 //   b_R = g5 R5 Omega_+ P_+ phi : b_R(s) = +Omega_-(s) phi_upper
@@ -195,24 +164,6 @@ hipError_t launch_gauge_convert(int po, const void* in, void* out, size_t n, hip
 static Geo make_geo(const int L[4], int Ls) {
     const int V = L[0] * L[1] * L[2] * L[3];
     return Geo{{L[0], L[1], L[2], L[3]}, V, V / 2, Ls, 0};
-}
-
-hipError_t launch_nat5_to_dev(const void* nat, void* de, void* dodd, const int L[4], int Ls, size_t N,
-                              hipStream_t st) {
-    Geo g = make_geo(L, Ls);
-    const size_t n = 2 * (size_t)g.Vh * Ls;
-    hipLaunchKernelGGL(k_nat5_to_dev, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-                       (const double2*)nat, (double2*)de, (double2*)dodd, g, N);
-    return hipGetLastError();
-}
-
-hipError_t launch_dev_to_nat5(void* nat, const void* de, const void* dodd, const int L[4], int Ls,
-                              size_t N, hipStream_t st) {
-    Geo g = make_geo(L, Ls);
-    const size_t n = 2 * (size_t)g.Vh * Ls;
-    hipLaunchKernelGGL(k_dev_to_nat5, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-                       (double2*)nat, (const double2*)de, (const double2*)dodd, g, N);
-    return hipGetLastError();
 }
 
 hipError_t launch_eofa_source(const void* phi, const double* om, void* bLe, void* bLo, void* bRe,

@@ -87,8 +87,6 @@ constexpr int FT_STR = FT_SLOTS + 1;            // odd: the records' 12 words sp
 constexpr int FT_CHUNKS = FT_SLOTS * 12;        // 16-byte words of one staged slice
 constexpr int FT_LOADS = (FT_CHUNKS + 255) / 256;
 
-typedef double d2v __attribute__((ext_vector_type(2)));
-
 struct ForceTile {
     int lg[4];   // log2 of the tile extents (1 or 2)
     int n[4];    // tiles along each direction

@@ -289,6 +289,71 @@ struct HopArgs {
     // [D5+, D5-, D5inv+, D5inv-], each Ls x Ls row major; an Op5 of kind 3
     // applies D5 (a = 0) or D5^-1 (a = 1), transposed when tr != 0
     const double* dmat;
+    // natural-layout operands of dwf_apply's FP64 hops (the NAT kernels): aux is
+    // read from and out written to complex128 5D fields; zero_pair also writes
+    // zeros to the opposite-parity site of each output site's pair (the even
+    // sites of the Schur complement's output)
+    const void* aux_nat;
+    void* out_nat;
+    int zero_pair;
+    int L[4];
 };
+
+// ---------------------------------------------------------------------------
+// Rows of natural-layout 5D fields through an LDS tile.  A row is one 5D
+// site's 12 complex numbers, 192 contiguous bytes in the natural layout and
+// STR doubles apart in the tile; rowoff[r] is the row's offset in complex
+// numbers ((s V + i) 12 < 2^32) or NO_ROW.  Consecutive work-items take
+// consecutive 16-byte words, so a wavefront covers 5 1/3 whole records, where
+// one work-item per record would touch 64 lines per load.  Called by every
+// work-item; the caller synchronises.
+// ---------------------------------------------------------------------------
+constexpr int STR = 25;   // odd row stride: column sweeps of the tile are free of bank conflicts
+constexpr uint32_t NO_ROW = 0xffffffffu;
+typedef double d2v __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ void nat_rows_load(const void* __restrict__ nat, const uint32_t* rowoff, int nrow,
+                                              double* T) {
+    const d2v* src = reinterpret_cast<const d2v*>(nat);
+    const int NT = blockDim.x, n = nrow * 12;
+    constexpr int B = 4;   // loads in flight per batch
+    for (int e0 = threadIdx.x; e0 < n; e0 += B * NT) {
+        d2v v[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            const int e = min(e0 + u * NT, n - 1), r = e / 12;
+            const uint32_t o = rowoff[r];
+            v[u] = src[(size_t)(o == NO_ROW ? 0u : o) + (uint32_t)(e - 12 * r)];
+        }
+#pragma unroll
+        for (int u = 0; u < B; ++u) {
+            const int e = min(e0 + u * NT, n - 1), r = e / 12;
+            double* d = T + r * STR + 2 * (e - 12 * r);
+            d[0] = v[u].x;
+            d[1] = v[u].y;
+        }
+    }
+}
+
+// zero_pair: the record of the other site of each pair (2 cb, 2 cb + 1) is cleared too
+__device__ __forceinline__ void nat_rows_store(void* __restrict__ nat, const uint32_t* rowoff, int nrow,
+                                               const double* T, bool zero_pair) {
+    d2v* dst = reinterpret_cast<d2v*>(nat);
+    const int NT = blockDim.x, n = nrow * 12;
+    for (int e = threadIdx.x; e < n; e += NT) {
+        const int r = e / 12, c = e - 12 * r;
+        const uint32_t o = rowoff[r];
+        if (o == NO_ROW) continue;
+        const double* s = T + r * STR + 2 * c;
+        d2v v = {s[0], s[1]};
+        __builtin_nontemporal_store(v, dst + (size_t)o + c);
+        if (zero_pair) {
+            // row offsets are multiples of 12; V is even, so the parity of o / 12 is that of the site index
+            const uint32_t z = ((o / 12u) & 1u) ? o - 12u : o + 12u;
+            v = d2v{0.0, 0.0};
+            __builtin_nontemporal_store(v, dst + (size_t)z + c);
+        }
+    }
+}
 
 }  // namespace eofa

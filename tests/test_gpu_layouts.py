@@ -1,0 +1,55 @@
+"""Natural <-> device layout passes and the FP64 operator whose last hop reads
+and writes the natural layout, at the edges of their workgroups: Ls that
+leaves ragged rows, the largest Ls, lattices with inactive rows, block and
+per-site hops, against the oracle; in reduced precision against the stated
+bounds.  The even sites of a Schur complement's input may hold anything."""
+import numpy as np
+import pytest
+
+import dwf_inputs as din
+import oracle
+from helpers import PREC_TOL, region_rel, rel, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("L,Ls", [((2, 2, 2, 2), 1), ((2, 2, 2, 2), 64), ((4, 6, 2, 10), 5), ((6, 2, 4, 6), 13),
+                                  ((4, 4, 4, 4), 24), ((2, 4, 6, 2), 32), ((10, 4, 2, 4), 18)])
+def test_apply_layouts(L, Ls):
+    import torch
+    from paper_1611_00298_amd import Context
+    mp, mm = 0.07, 0.6
+    U, psi = din.random_gauge(L, 0.4, 711), din.gaussian_5d(L, Ls, 712)
+    lat = oracle.Lattice(L, Ls, M5=1.8, alpha=2.0)
+    with Context(L, Ls, to_dev(U), M5=1.8, alpha=2.0) as ctx:
+        x = to_dev(psi)
+        t, z, y, w = np.indices(psi.shape[1:5])
+        odd = (t + z + y + w) % 2 == 1
+        xo = x.clone()
+        xo[:, to_dev(~odd)] = float("nan")
+        for dag in (False, True):
+            full, schur = oracle.ddwf(lat, U, mp, mm, psi, dagger=dag), oracle.schur(lat, U, mp, mm, psi, dagger=dag)
+            for prec in ("fp64", "fp32", "fp16", "bf16"):
+                print(f"layouts: L={L} Ls={Ls} dagger={dag} {prec}", flush=True)
+                out = torch.full_like(x, float("nan"))
+                ctx.dwf_apply(x, mp, mm, dagger=dag, prec=prec, out=out)
+                assert region_rel(out.cpu().numpy(), full) <= PREC_TOL[prec]
+                out.fill_(float("nan"))
+                ctx.dwf_apply(xo if prec == "fp64" else x, mp, mm, dagger=dag, eo=True, prec=prec, out=out)
+                o = out.cpu().numpy()
+                assert rel(o, schur) <= PREC_TOL[prec]
+                assert not o[:, ~odd].any()
+
+
+def test_solution_layout_round_trip():
+    """A converged solution handed back as the guess: the two layout passes
+    return it, and the solve needs no iterations."""
+    from paper_1611_00298_amd import Context
+    L, Ls = (4, 6, 2, 4), 5
+    U, phi = din.random_gauge(L, 0.4, 721), din.gaussian_4d(L, 722)
+    with Context(L, Ls, to_dev(U), M5=1.8, alpha=2.0) as ctx:
+        cl, cr, _, S, st = ctx.eofa_solve(to_dev(phi), 0.1, 0.8, tol=1e-12)
+        assert min(st["iters"]) > 0
+        cl2, cr2, _, S2, st2 = ctx.eofa_solve(to_dev(phi), 0.1, 0.8, tol=1e-11, x0=(cl, cr))
+        assert st2["iters"] == [0, 0]
+        assert rel(cl2.cpu().numpy(), cl.cpu().numpy()) <= 1e-13 and rel(cr2.cpu().numpy(), cr.cpu().numpy()) <= 1e-13
