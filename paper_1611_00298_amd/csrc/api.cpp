@@ -29,8 +29,8 @@ hipError_t launch_hop(int prec, bool dag, bool hop, const HopArgs& a, int nblk, 
 int hop_occupancy(int prec, bool mfma, bool blk, int NS, int Ls);
 hipError_t launch_pupdate(int prec, const void* z, const float* zn, const void* po, const float* pon,
                           void* p, float* pn, void* pt,
-                          float* ptn, const double* sc, int i_new, int i_old, int first, int Vh,
-                          int Ls, int NS, size_t N, double b5, double c5, double mp, double mm,
+                          float* ptn, const double* sc, int i_new, int i_old, int first, const double* part,
+                          int npart, const RedOut& ro, int Vh, int Ls, int NS, size_t N, double b5, double c5, double mp, double mm,
                           int nblk, hipStream_t st);
 hipError_t launch_r_update(int prec, void* r, float* rn, const void* w, const float* wn, double* sc,
                            int i_num, int i_den, int i_save, size_t n5, size_t N, double* partial,
@@ -39,7 +39,7 @@ hipError_t launch_x_batch(int prec, void* x, float* xn, const void* const* p, co
                           const int* slots, int cnt, const double* sc, size_t n5, size_t N, int nblk,
                           hipStream_t st);
 int blas_blocks(size_t n5);
-hipError_t launch_reduce(const double* partial, int n, double* out, int slot, hipStream_t st);
+hipError_t launch_reduce(const double* partial, int n, const RedOut& ro, hipStream_t st);
 hipError_t launch_norm2(int prec, const void* f, const float* fn, size_t n5, size_t N,
                         double* partial, int nblk, hipStream_t st);
 hipError_t launch_convert(int pi, int po, const void* in, const float* inn, void* out, float* outn,
@@ -317,6 +317,8 @@ struct HopCall {
     const void* aux_nat = nullptr;
     void* out_nat = nullptr;
     bool zero_pair = false;
+    // daggered hops below FP64: also sum the red_n partials of an earlier launch into scalar slot red_slot
+    int red_n = 0, red_slot = 0;
 };
 
 void run_hop(eofa_ctx* c, const HopCall& h) {
@@ -393,6 +395,13 @@ void run_hop(eofa_ctx* c, const HopCall& h) {
         a.s_den = h.s_den;
         a.s_alpha = h.s_alpha;
     }
+    if (h.red_n) {
+        if (h.partial) fail(EOFA_EDEVICE, "internal: a hop cannot reduce the partials it writes");
+        a.red_in = c->partial;
+        a.red_n = h.red_n;
+        a.red_slot = h.red_slot;
+        a.dsc_red = c->sc;
+    }
     // bookkeeping: flops (fixed convention) and algorithmic bytes
     double f = 0, nfields = 1;
     if (h.hop) f += 1320.0 + op_flops(h.A, c->Ls), nfields += 1;
@@ -440,13 +449,14 @@ void local_op(eofa_ctx* c, int prec, const Half& in, Half& out, Op5 B, Op5 C, do
     run_hop(c, h);
 }
 
-void reduce(eofa_ctx* c, int n, int slot) {
-    hipchk(launch_reduce(c->partial, n, c->sc, slot, c->st), "reduce");
+// sum of the first n partials into scalar slot `slot` (and slots [first, first + cnt) to host memory)
+void reduce(eofa_ctx* c, int n, int slot, double* host = nullptr, int first = 0, int cnt = 0) {
+    hipchk(launch_reduce(c->partial, n, RedOut{c->sc, slot, host, first, cnt}, c->st), "reduce");
 }
 
-double read_slot(eofa_ctx* c, int slot) {
-    hipchk(hipMemcpyAsync(c->pinned + slot, c->sc + slot, sizeof(double), hipMemcpyDeviceToHost, c->st),
-           "hipMemcpy(scalar)");
+// the same sum on the host: the reduction writes it to pinned memory itself
+double reduce_read(eofa_ctx* c, int n, int slot) {
+    reduce(c, n, slot, c->pinned + slot, slot, 1);
     hipchk(hipStreamSynchronize(c->st), "hipStreamSynchronize");
     return c->pinned[slot];
 }
@@ -461,8 +471,7 @@ const double* read_slots(eofa_ctx* c, int first, int n) {
 
 double norm2(eofa_ctx* c, const Half& f, int slot) {
     hipchk(launch_norm2(f.prec, f.d, f.nrm, c->n5, c->N, c->partial, c->nblk_blas, c->st), "norm2");
-    reduce(c, c->nblk_blas, slot);
-    return read_slot(c, slot);
+    return reduce_read(c, c->nblk_blas, slot);
 }
 
 void convert(eofa_ctx* c, const Half& in, Half& out) {
@@ -514,9 +523,11 @@ void schur_k2_tilde(eofa_ctx* c, int prec, const Half& tmp, const Half& pt, Half
     h.aux = &pt; h.B = Mee(c, 0); h.B2 = DtInv(c, 0); h.ca = 1.0; h.mp = mp; h.mm = mm; h.partial = partial;
     run_hop(c, h);
 }
-// K3: tmp_e = M_ee^-dag Dtilde^dag Dh^dag_eo in_o
-void schur_k3(eofa_ctx* c, int prec, const Half& in, Half& tmp, double mp, double mm) {
+// K3: tmp_e = M_ee^-dag Dtilde^dag Dh^dag_eo in_o   (red_n > 0: and the sum of K2's partials into red_slot)
+void schur_k3(eofa_ctx* c, int prec, const Half& in, Half& tmp, double mp, double mm, int red_n = 0,
+              int red_slot = 0) {
     HopCall h;
+    h.red_n = red_n; h.red_slot = red_slot;
     h.prec = prec; h.dag = true; h.par = 0; h.in = &in; h.out = &tmp;
     h.A = Dt(c, 1); h.C = MeeInv(c, 1); h.mp = mp; h.mm = mm;
     run_hop(c, h);
@@ -544,12 +555,14 @@ void schur_k4_update(eofa_ctx* c, int prec, const Half& tmp, const Half& w, Half
 }
 
 // p <- z + beta p_old (or p <- z), pt <- Dtilde p; beta = sc[i_new] / sc[i_old]
-// (pt == nullptr: p <- Dtilde z + beta p, the direction kept in Cayley form)
+// (pt == nullptr: p <- Dtilde z + beta p, the direction kept in Cayley form; npart > 0: sc[i_new] is
+// first summed from npart partials, and slots S_WW.. S_WW + 2 go to host)
 void pupdate(eofa_ctx* c, int prec, const Half& z, const Half* pold, Half& p, Half* pt, int i_new, int i_old,
-             double mp, double mm) {
+             double mp, double mm, int npart = 0, double* host = nullptr) {
     const int ev = timing_begin(c);
     hipchk(launch_pupdate(prec, z.d, z.nrm, pold ? pold->d : nullptr, pold ? pold->nrm : nullptr, p.d, p.nrm,
-                          pt ? pt->d : nullptr, pt ? pt->nrm : nullptr, c->sc, i_new, i_old, pold ? 0 : 1, c->Vh,
+                          pt ? pt->d : nullptr, pt ? pt->nrm : nullptr, c->sc, i_new, i_old, pold ? 0 : 1,
+                          c->partial, npart, RedOut{c->sc, i_new, host, S_WW, 3}, c->Vh,
                           c->Ls, c->NS, c->N, c->b5, c->c5, mp, mm, c->nblk_hop, c->st),
            "pupdate");
     timing_end(c, ev, C_BLAS, (double)c->n5 * ((pold ? 3.0 : 2.0) + (pt ? 1.0 : 0.0)) * spinor_bytes(prec));
@@ -558,6 +571,12 @@ void pupdate(eofa_ctx* c, int prec, const Half& z, const Half* pold, Half& p, Ha
 void check_finite(double v, const char* what) {
     if (!std::isfinite(v)) fail(EOFA_ENAN, std::string("non-finite ") + what);
 }
+
+// Up to this many partials of |z|^2 are summed by every workgroup of the
+// direction update instead of a launch of its own.  12^3x24, Ls = 12 (1296
+// partials): a heatbath 472 ms against 480 ms; 16^3x32, Ls = 16 (4096): equal;
+// 24^3x16, Ls = 24 (13824): a solve 972 ms against 890 ms.
+constexpr int PUPD_PARTIALS = 2048;
 
 struct SolveResult {
     int iters = 0;
@@ -587,8 +606,7 @@ SolveResult cgnr_schur(eofa_ctx* c, double mp, double mm, const Half& bhat, Half
         h.aux = &x; h.B = Mee(c, 0); h.ca = -1.0; h.aux2 = &bhat; h.cr = 1.0;
         h.mp = mp; h.mm = mm; h.partial = c->partial;
         run_hop(c, h);
-        reduce(c, nb, S_RR);
-        return read_slot(c, S_RR);
+        return reduce_read(c, nb, S_RR);
     };
     double rr;
     if (guess) {
@@ -659,9 +677,12 @@ SolveResult cgnr_schur(eofa_ctx* c, double mp, double mm, const Half& bhat, Half
         // arithmetic, since (r_k, Mhat p_k) = (z_k, p_k) = |z_k|^2).  Reliable
         // updates replace the estimate by the FP64 true residual and z by
         // Mhat^dag of it; convergence is only declared on a true residual.
-        // The scalars of iteration k are copied to the host ring after its K4
-        // and read while iteration k+1 runs, so the host never waits on an
+        // The scalars of iteration k go to the host ring after its K4
+        // and are read while iteration k+1 runs, so the host never waits on an
         // idle GPU; decisions therefore use the estimate one iteration late.
+        // |z|^2 of at most PUPD_PARTIALS partials is summed by the direction
+        // update itself; more than that by a reduction of its own.
+        const bool in_p = nb <= PUPD_PARTIALS;
         double rr_est = rr;
         int pend_cur = -1;          // slot of |z_k|^2 of the pending ring entry, -1: none
         // Stagnation guard: in 16-bit arithmetic the recursion can stall
@@ -679,15 +700,15 @@ SolveResult cgnr_schur(eofa_ctx* c, double mp, double mm, const Half& bhat, Half
             Half& p = *pr[k % XBATCH];
             schur_k1(c, prec, p, tmp, mp, mm);
             schur_k2_tilde(c, prec, tmp, p, w, mp, mm, c->partial);
-            reduce(c, nb, S_WW);
-            schur_k3(c, prec, w, tmp, mp, mm);
+            if (prec == P64) reduce(c, nb, S_WW);
+            schur_k3(c, prec, w, tmp, mp, mm, prec == P64 ? 0 : nb, S_WW);   // and |w|^2 from K2's partials
             schur_k4_update(c, prec, tmp, w, z, mp, mm, cur, S_WW, S_ALPHA + k % XBATCH, c->partial);
-            reduce(c, nb, nxt);
             res.iters++;
             double* slot_k = c->ring + 4 * (k & 1);
-            hipchk(hipMemcpyAsync(slot_k, c->sc + S_WW, sizeof(double) * 3, hipMemcpyDeviceToHost, c->st),
-                   "hipMemcpy(scalars)");
-            hipchk(hipEventRecord(c->ring_ev[k & 1], c->st), "hipEventRecord");
+            if (!in_p) {
+                reduce(c, nb, nxt, slot_k, S_WW, 3);
+                hipchk(hipEventRecord(c->ring_ev[k & 1], c->st), "hipEventRecord");
+            }
             if (pend_cur >= 0) {   // iteration k-1
                 hipchk(hipEventSynchronize(c->ring_ev[(k - 1) & 1]), "hipEventSynchronize");
                 const double* sv = c->ring + 4 * ((k - 1) & 1);
@@ -731,12 +752,13 @@ SolveResult cgnr_schur(eofa_ctx* c, double mp, double mm, const Half& bhat, Half
                 convert(c, r64, r);
                 schur_k3(c, prec, r, tmp, mp, mm);
                 schur_k4(c, prec, tmp, r, z, mp, mm, c->partial);
-                reduce(c, nb, nxt);
+                if (!in_p) reduce(c, nb, nxt);
             }
             if (k - pending0 + 1 == XBATCH) flush(k);
             if (res.iters >= maxiter) { flush(k); break; }
             Half& pn1 = *pr[(k + 1) % XBATCH];
-            pupdate(c, prec, z, restart ? nullptr : &p, pn1, nullptr, nxt, cur, mp, mm);
+            pupdate(c, prec, z, restart ? nullptr : &p, pn1, nullptr, nxt, cur, mp, mm, in_p ? nb : 0, slot_k);
+            if (in_p) hipchk(hipEventRecord(c->ring_ev[k & 1], c->st), "hipEventRecord");
             c->flops += 72.0 * (double)c->n5 + 48.0 * (double)c->n5;
             std::swap(cur, nxt);
             ++k;
@@ -760,9 +782,8 @@ SolveResult cgnr_schur(eofa_ctx* c, double mp, double mm, const Half& bhat, Half
             timing_end(c, ev, C_BLAS, (double)c->n5 * 3.0 * spinor_bytes(prec));
             c->flops += 48.0 * (double)c->n5;
         }
-        reduce(c, c->nblk_blas, S_RR);
         res.iters++;
-        rr = read_slot(c, S_RR);
+        rr = reduce_read(c, c->nblk_blas, S_RR);
         check_finite(rr, "residual norm");
         if (std::sqrt(rr) <= thresh) {
             flush(k);
@@ -805,8 +826,8 @@ struct Forecast {
 void cdot64(eofa_ctx* c, const Half& a, const Half& b, double* re, double* im) {
     const int nb = c->nblk_blas;
     hipchk(launch_cdot64(a.d, b.d, c->n5, c->N, c->partial, nb, c->st), "cdot");
-    hipchk(launch_reduce(c->partial, nb, c->sc, S_T0, c->st), "reduce");
-    hipchk(launch_reduce(c->partial + nb, nb, c->sc, S_T1, c->st), "reduce");
+    hipchk(launch_reduce(c->partial, nb, RedOut{c->sc, S_T0, nullptr, 0, 0}, c->st), "reduce");
+    hipchk(launch_reduce(c->partial + nb, nb, RedOut{c->sc, S_T1, nullptr, 0, 0}, c->st), "reduce");
     const double* v = read_slots(c, S_T0, 2);
     *re = v[0];
     *im = v[1];
@@ -926,8 +947,7 @@ CayleyOut solve_cayley(eofa_ctx* c, double mp, double mm, const Half& be, const 
             h.partial = c->partial + (size_t)par * nb;
             run_hop(c, h);
         }
-        reduce(c, 2 * nb, S_T0);
-        const double rr = read_slot(c, S_T0);
+        const double rr = reduce_read(c, 2 * nb, S_T0);
         check_finite(rr, "true residual");
         out.true_resid = std::sqrt(rr) / bnorm;
         out.converged = out.true_resid <= sp.tol;
@@ -1080,8 +1100,7 @@ DenseOut solve_dense(eofa_ctx* c, const double* dm, const Half& be, const Half& 
     auto true_residual = [&]() -> double {
         dense_hop(c, dm, P64, false, 0, &xo, t64, D5Inv(0), 1.0, nullptr, I5, 0.0, nullptr, 0.0, nullptr);
         dense_hop(c, dm, P64, false, 1, &t64, s64, I5, 1.0, &xo, D5(0), -1.0, &bh, 1.0, c->partial);
-        reduce(c, nb, S_T1);
-        const double rr = read_slot(c, S_T1);
+        const double rr = reduce_read(c, nb, S_T1);
         check_finite(rr, "true residual");
         return std::sqrt(rr);
     };
@@ -1122,8 +1141,7 @@ DenseOut solve_dense(eofa_ctx* c, const double* dm, const Half& be, const Half& 
         // p = r = Mhat^dag s
         auto restart = [&]() -> double {
             mhat_dag(sr, r, c->partial);
-            reduce(c, nb, S_T0);
-            const double g = read_slot(c, S_T0);
+            const double g = reduce_read(c, nb, S_T0);
             check_finite(g, "dense CG");
             convert(c, r, p);
             return g;
@@ -1138,8 +1156,7 @@ DenseOut solve_dense(eofa_ctx* c, const double* dm, const Half& be, const Half& 
         bool stagnated = false;
         while (out.iters < sp.maxiter && gam > 0.0) {
             mhat(p, w, c->partial);
-            reduce(c, nb, S_T0);
-            const double ww = read_slot(c, S_T0);
+            const double ww = reduce_read(c, nb, S_T0);
             check_finite(ww, "dense CG");
             if (!(ww > 0.0)) break;
             const double alpha = gam / ww;
@@ -1149,10 +1166,9 @@ DenseOut solve_dense(eofa_ctx* c, const double* dm, const Half& be, const Half& 
                                   c->partial, c->nblk_blas, c->st),
                    "cg step");
             timing_end(c, ev, C_BLAS, (double)c->n5 * 6.0 * spinor_bytes(prec));
-            reduce(c, c->nblk_blas, S_T1);
             ++out.iters;
             ++seg_iters;
-            double rn = std::sqrt(read_slot(c, S_T1));
+            double rn = std::sqrt(reduce_read(c, c->nblk_blas, S_T1));
             check_finite(rn, "dense CG");
             const bool stalled = mixed && seg_iters > std::max(400, 4 * seg_max);
             const bool overdue = mixed && out.iters - it_halve > 1000;
@@ -1181,8 +1197,7 @@ DenseOut solve_dense(eofa_ctx* c, const double* dm, const Half& be, const Half& 
             }
             if (rn <= target) break;
             mhat_dag(sr, r, c->partial);
-            reduce(c, nb, S_T0);
-            const double g2 = read_slot(c, S_T0);
+            const double g2 = reduce_read(c, nb, S_T0);
             check_finite(g2, "dense CG");
             // p <- r + (g2 / gam) p
             dense_hop(c, dm, prec, false, 0, nullptr, p, I5, 1.0, &p, I5, g2 / gam, &r, 1.0, nullptr);
@@ -1200,8 +1215,7 @@ DenseOut solve_dense(eofa_ctx* c, const double* dm, const Half& be, const Half& 
     for (int par = 0; par < 2; ++par)
         dense_hop(c, dm, P64, false, par, par ? &xe : &xo, rt, I5, -1.0, par ? &xo : &xe, D5(0), -1.0,
                   par ? &bo : &be, 1.0, c->partial + (size_t)par * nb);
-    reduce(c, 2 * nb, S_T0);
-    const double rr = read_slot(c, S_T0);
+    const double rr = reduce_read(c, 2 * nb, S_T0);
     check_finite(rr, "true residual");
     out.true_resid = std::sqrt(rr) / bnorm;
     out.converged = out.true_resid <= sp.tol;
@@ -1247,8 +1261,7 @@ int solve_dense_impl(eofa_ctx* c, double m1, double m2, const void* phi, void* c
     if (S || Mphi) {
         const int nb = action_blocks(c->V);
         hipchk(launch_eofa_action(phi, chiL, chiR, c->om, k, Mphi, c->partial, c->V, c->Ls, c->st), "action");
-        reduce(c, nb, S_T1);
-        const double s = read_slot(c, S_T1);
+        const double s = reduce_read(c, nb, S_T1);
         check_finite(s, "action");
         if (S) *S = s;
     }
@@ -1334,8 +1347,7 @@ int solve_impl(eofa_ctx* c, double m1, double m2, const void* phi, const void* x
     if (S || Mphi) {
         const int nb = action_blocks(c->V);
         hipchk(launch_eofa_action(phi, chiL, chiR, c->om, k, Mphi, c->partial, c->V, c->Ls, c->st), "action");
-        reduce(c, nb, S_T1);
-        const double s = read_slot(c, S_T1);
+        const double s = reduce_read(c, nb, S_T1);
         check_finite(s, "action");
         if (S) *S = s;
     }
@@ -1539,8 +1551,7 @@ int bounds_impl(eofa_ctx* c, double m1, double m2, const void* start, int n_iter
     const int nb = dot4_blocks(c->V);
     auto dot = [&](const void* a, const void* b) {
         hipchk(launch_dot4(a, b, c->partial, c->V, c->st), "dot");
-        reduce(c, nb, S_T0);
-        const double r = read_slot(c, S_T0);
+        const double r = reduce_read(c, nb, S_T0);
         check_finite(r, "Lanczos inner product");
         return r;
     };
@@ -2108,8 +2119,7 @@ int eofa_md_update(eofa_ctx_t* c, void* U, void* P, const void* F, double dt_p, 
         const bool pf = F && dt_p != 0.0, uu = dt_u != 0.0;
         timing_end(c, ev, C_MD, (double)nlink * 144.0 * ((pf ? 3.0 : 1.0) + (uu ? 2.0 : 0.0)));
         if (kin) {
-            reduce(c, md_blocks(nlink), S_T1);
-            *kin = read_slot(c, S_T1);
+            *kin = reduce_read(c, md_blocks(nlink), S_T1);
         }
         return EOFA_OK;
     });
@@ -2131,7 +2141,7 @@ int eofa_md_update_noalloc(eofa_ctx_t* c, void* U, void* P, const void* F, doubl
         // the same kernels as eofa_md_update; every partial the reduction
         // reads is written by this call first, so nothing needs clearing
         hipchk(launch_md_update(U, P, F, dt_p, dt_u, nlink, scr, c->st), "md update");
-        if (kin_dev) hipchk(launch_reduce(scr, md_blocks(nlink), kin_dev, 0, c->st), "reduce");
+        if (kin_dev) hipchk(launch_reduce(scr, md_blocks(nlink), RedOut{kin_dev, 0, nullptr, 0, 0}, c->st), "reduce");
         return EOFA_OK;
     });
 }
@@ -2150,8 +2160,7 @@ int eofa_gauge_action(eofa_ctx_t* c, const void* U, double beta, double c1, doub
         hipchk(launch_gauge_action(U, c->L, c1, c->partial, c->st), "gauge action");
         // algorithmic bytes: every link read once
         timing_end(c, ev, C_GACTION, 4.0 * c->V * 144.0);
-        reduce(c, gauge_action_blocks(c->V), S_T1);
-        const double s = read_slot(c, S_T1);
+        const double s = reduce_read(c, gauge_action_blocks(c->V), S_T1);
         if (!std::isfinite(s)) fail(EOFA_ENAN, "gauge action is not finite");
         *S = beta * s;
         return EOFA_OK;

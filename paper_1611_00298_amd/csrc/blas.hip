@@ -30,14 +30,11 @@ __device__ __forceinline__ void block_store_sum(double x, double* dst) {
     }
 }
 
-// out[slot] = sum of partial[0..n) (one workgroup of 1024).  Thread j sums
-// partial[j], partial[j + 1024], ... in that order; the loads are issued 8 at
-// a time so that one workgroup is not bound by the latency of a chain of
-// dependent loads (a hop leaves one partial per workgroup: 55296 at 24^3x64).
-__global__ void __launch_bounds__(1024) k_reduce(const double* __restrict__ partial, int n,
-                                                 double* out, int slot) {
-    // each work-item adds its elements in index order; 32 loads are in
-    // flight at a time (a hop's 55 296 partials take two batches)
+// sum of partial[0..n) to ro (one workgroup of 1024).  Thread j sums
+// partial[j], partial[j + 1024], ... in that order; 32 loads are in flight at
+// a time (a hop leaves one partial per workgroup: 55296 at 24^3x64, two
+// batches), so that one workgroup is not bound by a chain of dependent loads.
+__global__ void __launch_bounds__(1024) k_reduce(const double* __restrict__ partial, int n, const RedOut ro) {
     double t = 0;
     const int step = blockDim.x;
     int i = threadIdx.x;
@@ -56,7 +53,9 @@ __global__ void __launch_bounds__(1024) k_reduce(const double* __restrict__ part
         for (int q = 0; q < 8; ++q) t += v[q];
     }
     for (; i < n; i += step) t += partial[i];
-    block_store_sum(t, out + slot);
+    __shared__ double sum;
+    block_store_sum(t, &sum);
+    if (threadIdx.x == 0) red_store(ro, sum);
 }
 
 // r -= alpha w ; partial |r|^2 ; alpha = sc[i_num] / sc[i_den], also kept in
@@ -289,8 +288,8 @@ hipError_t launch_cg_step(int prec, void* x, const void* p, const float* pn, voi
     return hipGetLastError();
 }
 
-hipError_t launch_reduce(const double* partial, int n, double* out, int slot, hipStream_t st) {
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(1024), 0, st, partial, n, out, slot);
+hipError_t launch_reduce(const double* partial, int n, const RedOut& ro, hipStream_t st) {
+    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(1024), 0, st, partial, n, ro);
     return hipGetLastError();
 }
 

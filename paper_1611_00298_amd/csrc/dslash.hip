@@ -1160,6 +1160,8 @@ __device__ __forceinline__ double block_sum(double x, double* red) {
 template <int P, bool DAG, bool HOP, int MF, bool DENSE = false, bool BLK = false, bool NAT = false>
 __global__ void __launch_bounds__(256, (MF == 3 && P == P16 && !DENSE) ? 5 : 3) k_hop(const HopArgs a) {
     using A = typename PT<P>::A;
+    // (FP64 would spill more: its reductions stay launches of their own)
+    constexpr bool RED = P != P64 && DAG && HOP && !DENSE;
     // column-sweep load batch: what each variant's register budget allows
     constexpr int COLB = P == P64 ? 1 : (P == P16 && MF) ? 4 : 8;
     extern __shared__ unsigned char smem_raw[];
@@ -1170,7 +1172,19 @@ __global__ void __launch_bounds__(256, (MF == 3 && P == P16 && !DENSE) ? 5 : 3) 
     const int Ls = a.Ls;
     const int sl = tid / Ls;
     const int s = tid - sl * Ls;
-    const int lb = xcd_block(gridDim.x);
+    int blk = blockIdx.x, nblk = gridDim.x;
+    if constexpr (RED) {
+        if (a.red_n) {   // the first workgroup reduces, the others are the hop's
+            if (blk == 0) {
+                const double t = sum_partials(a.red_in, a.red_n, red);
+                if (tid == 0) a.dsc_red[a.red_slot] = t;
+                return;
+            }
+            --blk;
+            --nblk;
+        }
+    }
+    const int lb = xcd_block(nblk, blk);
     const int slot = lb * a.NS + sl;
     const int site = a.sites ? a.sites[slot] : slot;
     const bool active = site < a.Vh;
@@ -1241,7 +1255,7 @@ __global__ void __launch_bounds__(256, (MF == 3 && P == P16 && !DENSE) ? 5 : 3) 
     double alpha = 1.0;
     if (a.dsc) {
         alpha = a.dsc[a.s_num] / a.dsc[a.s_den];
-        if (a.s_alpha >= 0 && blockIdx.x == 0 && tid == 0) a.dsc[a.s_alpha] = alpha;
+        if (a.s_alpha >= 0 && blk == 0 && tid == 0) a.dsc[a.s_alpha] = alpha;
     }
     if (HOP) {
         A ch = (A)(a.ch * alpha);
@@ -1344,7 +1358,7 @@ __global__ void __launch_bounds__(256, (MF == 3 && P == P16 && !DENSE) ? 5 : 3) 
             x = (double)q;
         }
         x = block_sum(x, red);
-        if (tid == 0) a.partial[blockIdx.x] = x;   // order-independent slot
+        if (tid == 0) a.partial[blk] = x;   // order-independent slot
     }
 }
 
@@ -1353,13 +1367,15 @@ __global__ void __launch_bounds__(256, (MF == 3 && P == P16 && !DENSE) ? 5 : 3) 
 // Schur application:  p <- z + beta p  (beta = sc[i1]/sc[i0], or p <- z on
 // the first call), pt <- Dtilde p = (b5 + c5 L) p.  With pt == nullptr only
 // the Cayley-transformed direction is kept: p <- Dtilde z + beta p.
+// npart > 0 (that form only): sc[i_new] is still in its npart partials; every
+// workgroup sums them, the first one stores the result through `ro`.
 // ---------------------------------------------------------------------------
 template <int P>
 __global__ void __launch_bounds__(256) k_pupdate(const void* z, const float* z_nrm, const void* pold,
                                                  const float* pold_nrm, void* p,
                                                  float* p_nrm, void* pt, float* pt_nrm,
                                                  const double* sc, int i_new, int i_old, int first,
-                                                 int Vh, int Ls, int NS, size_t N, double b5,
+                                                 const double* part, int npart, const RedOut ro, int Vh, int Ls, int NS, size_t N, double b5,
                                                  double c5, double mp_, double mm_) {
     using A = typename PT<P>::A;
     extern __shared__ unsigned char smem_raw[];
@@ -1376,13 +1392,21 @@ __global__ void __launch_bounds__(256) k_pupdate(const void* z, const float* z_n
     if (!pt) {
         // search directions kept as pt = Dtilde p:  pt <- Dtilde z + beta pt_old
         if (active) ld_spinor<P>(z, z_nrm, N, n, v);
+        double znew = 0;
+        if (npart) {
+            __shared__ double red[16];
+            znew = sum_partials(part, npart, red);
+            if (blockIdx.x == 0 && tid == 0) red_store(ro, znew);
+        } else if (!first) {
+            znew = sc[i_new];
+        }
         put_row(lds, tid, v);
         __syncthreads();
         A t[24];
         row_bidiag(lds, tid, s, Ls, v, t, (A)b5, (A)c5, 0, (A)mp_, (A)mm_);
         if (active) {
             if (!first) {
-                const A beta = (A)(sc[i_new] / sc[i_old]);
+                const A beta = (A)(znew / sc[i_old]);
                 A q[24];
                 ld_spinor<P>(pold, pold_nrm, N, n, q);
 #pragma unroll
@@ -1555,6 +1579,10 @@ hipError_t launch_dev_to_nat(int prec, void* nat, void* e, float* en, void* o, f
 template <int P, bool DAG, bool HOP>
 static hipError_t launch_hop_t(const HopArgs& a, int nblk, hipStream_t st) {
     using A = typename PT<P>::A;
+    if (a.red_n) {
+        if (P == P64 || !DAG || !HOP) return hipErrorInvalidValue;
+        ++nblk;
+    }
     const int NT = a.NS * a.Ls;
     const bool need_lds = HOP ? (a.opA.kind != 0 || a.opC.kind != 0 || (a.aux && (a.opB.kind != 0 || a.opB2.kind != 0)))
                               : (a.opB.kind != 0 || a.opC.kind != 0);
@@ -1683,8 +1711,8 @@ hipError_t launch_hop(int prec, bool dag, bool hop, const HopArgs& a, int nblk, 
 
 hipError_t launch_pupdate(int prec, const void* z, const float* zn, const void* po, const float* pon,
                           void* p, float* pn, void* pt,
-                          float* ptn, const double* sc, int i_new, int i_old, int first, int Vh,
-                          int Ls, int NS, size_t N, double b5, double c5, double mp, double mm,
+                          float* ptn, const double* sc, int i_new, int i_old, int first, const double* part,
+                          int npart, const RedOut& ro, int Vh, int Ls, int NS, size_t N, double b5, double c5, double mp, double mm,
                           int nblk, hipStream_t st) {
     const int NT = NS * Ls;
     switch (prec) {
@@ -1692,7 +1720,7 @@ hipError_t launch_pupdate(int prec, const void* z, const float* zn, const void* 
     case PP: {                                                                                \
         const size_t shm = (size_t)STR * NT * sizeof(typename PT<PP>::A);                     \
         hipLaunchKernelGGL((k_pupdate<PP>), dim3(nblk), dim3(NT), shm, st, z, zn, po, pon, p, pn, pt, \
-                           ptn, sc, i_new, i_old, first, Vh, Ls, NS, N, b5, c5, mp, mm);      \
+                           ptn, sc, i_new, i_old, first, part, npart, ro, Vh, Ls, NS, N, b5, c5, mp, mm); \
         return hipGetLastError();                                                             \
     }
         EOFA_CASE(P64)

@@ -209,12 +209,57 @@ constexpr int XBATCH = 16;
 // Workgroups are dispatched round-robin over the 8 XCDs, each with its own
 // L2.  Renumber them so that XCD x works on one contiguous range of
 // logical blocks (neighbouring 4D sites then share an L2).
-__device__ __forceinline__ int xcd_block(int nblk) {
+__device__ __forceinline__ int xcd_block(int nblk, int b) {
     constexpr int NX = 8;
-    const int b = blockIdx.x;
     const int per = nblk / NX, rem = nblk % NX;
     const int x = b % NX, q = b / NX;
     return x * per + (x < rem ? x : rem) + q;
+}
+__device__ __forceinline__ int xcd_block(int nblk) { return xcd_block(nblk, blockIdx.x); }
+
+// Sum of partial[0..n) over the workgroup, the same bits in every work-item:
+// work-item j adds partial[j], partial[j + NT], ... in that order, then the
+// wavefronts' sums in theirs.  red: 16 doubles of LDS; one barrier.
+__device__ __forceinline__ double sum_partials(const double* __restrict__ partial, int n, double* red) {
+    const int NT = blockDim.x;
+    double t = 0;
+    int i = threadIdx.x;
+    for (; i + 15 * NT < n; i += 16 * NT) {   // a batch of loads in flight
+        double v[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) v[q] = partial[i + q * NT];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) t += v[q];
+    }
+    for (; i + 3 * NT < n; i += 4 * NT) {
+        double v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = partial[i + q * NT];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) t += v[q];
+    }
+    for (; i < n; i += NT) t += partial[i];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
+    __syncthreads();
+    t = 0;
+    for (int w = 0; w < (NT + 63) >> 6; ++w) t += red[w];
+    return t;
+}
+
+// Where a reduction kernel leaves its result: out[slot], and out[first..first + cnt)
+// (this slot included) in pinned host memory, if host is given.
+struct RedOut {
+    double* out;
+    int slot;
+    double* host;
+    int first, cnt;
+};
+__device__ __forceinline__ void red_store(const RedOut& r, double t) {
+    r.out[r.slot] = t;
+    if (r.host)
+        for (int i = 0; i < r.cnt; ++i) r.host[i] = r.first + i == r.slot ? t : r.out[r.first + i];
 }
 
 // ---------------------------------------------------------------------------
@@ -285,6 +330,11 @@ struct HopArgs {
     // dsc[s_num] / dsc[s_den], which is also stored to dsc[s_alpha] (>= 0)
     double* dsc;
     int s_num, s_den, s_alpha;
+    // with red_n > 0 (daggered hops below FP64) the launch has one workgroup more, which sums the
+    // red_n partials an earlier launch left into dsc_red[red_slot]
+    const double* red_in;
+    int red_n, red_slot;
+    double* dsc_red;
     // dense 5D blocks of D_EOFA's even-odd form (the dense comparison path, FP64, FP32 or FP16):
     // [D5+, D5-, D5inv+, D5inv-], each Ls x Ls row major; an Op5 of kind 3
     // applies D5 (a = 0) or D5^-1 (a = 1), transposed when tr != 0
