@@ -162,6 +162,7 @@ struct eofa_ctx {
     double M5 = 0, alpha = 0, b5 = 0, c5 = 0, beta0 = 0, beta1 = 0;
     size_t n5 = 0, N = 0;
     int NS = 0, nblk_hop = 0, nblk_blas = 0;
+    bool small_grid = false;   // the hop's grid leaves the GPU mostly idle: the latency form
     int* nbr = nullptr;
     int* sites[4] = {nullptr, nullptr, nullptr, nullptr};   // hop traversal (site per slot) per precision
     int blk[4] = {0, 0, 0, 0};   // the table lists whole 2x2x2x2 blocks (FP32 and matrix-core paths)
@@ -379,6 +380,8 @@ void run_hop(eofa_ctx* c, const HopCall& h) {
     a.Ls = c->Ls;
     a.NS = c->NS;
     a.N = c->N;
+    a.lat = h.hop && !h.dmat && !a.blk && c->small_grid;
+    if (a.lat) a.sites = nullptr;   // small fields: no order to gain, one dependent load less
     a.mp = h.mp;
     a.mm = h.mm;
     a.opA = h.A;
@@ -1876,6 +1879,20 @@ int eofa_ctx_create(eofa_ctx_t** out, const eofa_geom_t* g, const void* U, void*
             for (int q = ns; q >= 1; --q)
                 if ((q * c->Ls) % 64 == 0) { best = q; break; }
             c->NS = best;
+            int blocks_env = 1;
+            if (const char* e = getenv("EOFA_BLOCKS")) blocks_env = atoi(e);   // tuning: 0 per-site, 2 block-sharing hops on any grid
+            // Small lattices (at most one wavefront per SIMD): the hop is bound
+            // by its chain of dependent accesses, not by throughput, so the
+            // workgroups shrink to one wavefront, which spreads the links and
+            // barriers over more CUs, and the hop takes its latency form.  FP64
+            // solve on 4^4, Ls = 8: 18.2 -> 16.4 ms over the latency form alone
+            // (20.6 ms without); 8^3x16, Ls = 8 (512 wavefronts): a trajectory
+            // 182 -> 172 ms (202 ms).  Beyond it other wavefronts hide the
+            // latency: 1440 wavefronts 74.6 against 75.9 ms in the latency form,
+            // 3888 472 against 495 ms.
+            const int ns1 = std::max(1, 64 / c->Ls);
+            c->small_grid = blocks_env == 1 && (long)((c->Vh + ns1 - 1) / ns1) * ((ns1 * c->Ls + 63) / 64) <= 1024;
+            if (c->small_grid) c->NS = ns1;
             if (const char* e = getenv("EOFA_NS")) {   // tuning override: sites per workgroup
                 const int q = atoi(e);
                 if (q >= 1 && q <= 24 && q * c->Ls <= 256) c->NS = q;
@@ -1903,9 +1920,7 @@ int eofa_ctx_create(eofa_ctx_t** out, const eofa_geom_t* g, const void* U, void*
             // matrix-core paths, whenever a workgroup holds whole 2x2x2x2 blocks
             // and the block form's extra LDS costs no workgroups per CU (at
             // Ls = 8 the links of 24 sites per workgroup already fill it)
-            bool blocks_ok = c->NS % 8 == 0;
-            int blocks_env = 1;
-            if (const char* e = getenv("EOFA_BLOCKS")) blocks_env = atoi(e);   // tuning: 0 off, 2 forced
+            bool blocks_ok = c->NS % 8 == 0 && !c->small_grid;
             blocks_ok = blocks_ok && blocks_env != 0;
             const bool mf_ok = c->use_mfma && c->Ls % 4 == 0;
             for (int p = 0; p < 4; ++p) {

@@ -132,19 +132,19 @@ __host__ __device__ constexpr size_t stage_bytes(int lb_bytes, int NS) {
 // the site is the work-item's own, so no load waits on a table lookup.  FP64
 // also stages the slot's 8 neighbour indices, placed after the links.
 // Elements past the last repeat it (the same value to the same place).
-template <int P>
-__device__ __forceinline__ void stage_links(const HopArgs& a, int site, int sl, int s, unsigned char* lds) {
+template <int P, bool LAT = false>
+__device__ __forceinline__ void stage_links(const HopArgs& a, int site, int sl, int s, unsigned char* lds, int qs) {
     constexpr int LB = LinkLds<P, 0>::LB;
     using T = typename std::conditional<P == P64, double2, float2>::type;
     const int Ls = a.Ls;
-    if constexpr (P == P64) {
+    if constexpr (P == P64 && !LAT) {
         int* nbl = reinterpret_cast<int*>(lds + (size_t)a.NS * 8 * LB) + sl * 8;
         for (int d = s; d < 8; d += Ls) nbl[d] = a.nbr[(size_t)d * a.Vh + site];
     }
     const size_t bb = (size_t)a.Vh * sizeof(T);
     const uint32_t off = (uint32_t)site * (uint32_t)sizeof(T);
     unsigned char* rec = lds + (size_t)sl * 8 * LB;
-    for (int q0 = s; q0 < 72; q0 += 4 * Ls) {
+    for (int q0 = qs; q0 < 72; q0 += 4 * Ls) {
         T v[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) v[u] = at<T>(a.gauge, (size_t)min(q0 + u * Ls, 71) * bb, off);
@@ -198,8 +198,8 @@ __device__ __forceinline__ void stage_links_tbl(const HopArgs& a, int lb, unsign
 // links_put writes them to LDS, so that its writes wait for the links alone
 // while the gathers stay in flight; elements beyond the first K (Ls < 16)
 // are staged by links_put in further batches of K.
-template <int P, int MF> struct LinkPre {
-    static constexpr int K = 4;
+template <int P, int MF, int KK = 4> struct LinkPre {
+    static constexpr int K = KK;
     static constexpr int W = MF ? 3 : 2;   // 32-bit words per element
     static constexpr int E = MF ? 64 : 72; // elements per slot
     uint32_t w[K][W];
@@ -286,11 +286,11 @@ __device__ __forceinline__ void links_put(const HopArgs& a, int lb, const LinkPr
 // have to wait behind the gathers): work-item (sl, s) builds rows
 // q = s, s + Ls, ... of its slot's 8 records (q = 8 d + r); rows past the
 // last repeat it (a zero row).
-template <int P>
-__device__ __forceinline__ void links_load_site(const HopArgs& a, int site, int q0, LinkPre<P, 1>& pre) {
+template <int P, int K = 4>
+__device__ __forceinline__ void links_load_site(const HopArgs& a, int site, int q0, LinkPre<P, 1, K>& pre) {
     const uint32_t* g = reinterpret_cast<const uint32_t*>(a.frag);
 #pragma unroll
-    for (int u = 0; u < LinkPre<P, 1>::K; ++u) {
+    for (int u = 0; u < K; ++u) {
         const int q = min(q0 + u * a.Ls, 63), d = q >> 3, r = q & 7;
         const uint32_t* w = g + ((size_t)d * a.Vh + site) * 9 + 3 * (min(r, 5) >> 1);
 #pragma unroll
@@ -298,12 +298,12 @@ __device__ __forceinline__ void links_load_site(const HopArgs& a, int site, int 
     }
 }
 
-template <int P>
-__device__ __forceinline__ void links_write_site(const HopArgs& a, int sl, int q0, const LinkPre<P, 1>& pre,
+template <int P, int K = 4>
+__device__ __forceinline__ void links_write_site(const HopArgs& a, int sl, int q0, const LinkPre<P, 1, K>& pre,
                                                  unsigned char* lds) {
     constexpr int LB = LinkLds<P, 1>::LB;
 #pragma unroll
-    for (int u = 0; u < LinkPre<P, 1>::K; ++u) {
+    for (int u = 0; u < K; ++u) {
         const int q = min(q0 + u * a.Ls, 63), d = q >> 3, r = q & 7;   // row r as in links_write
         const uint32_t w0 = pre.w[u][0], w1 = pre.w[u][1], w2 = pre.w[u][2];
         uint4 v = (r & 1) ? make_uint4(__builtin_amdgcn_alignbit(w0, w0, 16), __builtin_amdgcn_alignbit(w1, w1, 16),
@@ -314,18 +314,19 @@ __device__ __forceinline__ void links_write_site(const HopArgs& a, int sl, int q
     }
 }
 
-template <int P>
-__device__ __forceinline__ void links_put_site(const HopArgs& a, int site, int sl, int s, const LinkPre<P, 1>& pre,
+template <int P, int K = 4>
+__device__ __forceinline__ void links_put_site(const HopArgs& a, int site, int sl, int s, const LinkPre<P, 1, K>& pre,
                                                unsigned char* lds) {
-    constexpr int K = LinkPre<P, 1>::K;
-    links_write_site<P>(a, sl, s, pre, lds);
+    links_write_site<P, K>(a, sl, s, pre, lds);
 #pragma unroll 1
     for (int q0 = s + K * a.Ls; q0 < 64; q0 += K * a.Ls) {
-        LinkPre<P, 1> more;
-        links_load_site<P>(a, site, q0, more);
-        links_write_site<P>(a, sl, q0, more, lds);
+        LinkPre<P, 1, K> more;
+        links_load_site<P, K>(a, site, q0, more);
+        links_write_site<P, K>(a, sl, q0, more, lds);
     }
 }
+
+typedef float f2v __attribute__((ext_vector_type(2)));
 
 // One direction's neighbour spinor, loaded ahead of its use.
 template <int P> struct Stage {
@@ -398,10 +399,43 @@ __device__ __forceinline__ void compute_stage_rt(const Stage<P>& st, int d, cons
 // registers allow no more), links from LDS.  Every work-item of the
 // workgroup must call this (it contains the staging barrier); padding
 // work-items pass site 0 and discard the result.
-template <int P, bool DAG, bool DENSE>
+// LAT (grids that leave the GPU mostly idle): the links' and then 8 (FP64: 4)
+// neighbour spinors' loads are all issued before anything waits.
+template <int P, bool DAG, bool DENSE, bool LAT>
 __device__ __forceinline__ void hop_all(const HopArgs& a, int lb, unsigned char* lds, int site, int sl, int s,
                                         typename PT<P>::A (&acc)[24]) {
     constexpr int LB = LinkLds<P, 0>::LB;
+    if constexpr (LAT) {
+        constexpr int DEPTH = P == P64 ? 4 : 8, K = 9;   // 9 link elements per work-item at Ls = 8
+        using T = typename std::conditional<P == P64, d2v, f2v>::type;
+        int nb[8];
+#pragma unroll
+        for (int d = 0; d < 8; ++d) nb[d] = a.nbr[(size_t)d * a.Vh + site];
+        T v[K];
+        const size_t bb = (size_t)a.Vh * sizeof(T);
+        const uint32_t off = (uint32_t)site * (uint32_t)sizeof(T);
+#pragma unroll
+        for (int u = 0; u < K; ++u) v[u] = at<T>(a.gauge, (size_t)min(s + u * a.Ls, 71) * bb, off);
+        __builtin_amdgcn_sched_barrier(0);
+        Stage<P> st[DEPTH];
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) load_stage<P>(a, s, nb[d], st[d], true);
+        __builtin_amdgcn_sched_barrier(0);
+        unsigned char* rec = lds + (size_t)sl * 8 * LB;
+#pragma unroll
+        for (int u = 0; u < K; ++u) {
+            const int q = min(s + u * a.Ls, 71), d = q / 9, k = q - 9 * d;
+            *reinterpret_cast<T*>(rec + d * LB + sizeof(T) * k) = v[u];
+        }
+        stage_links<P, true>(a, site, sl, s, lds, s + K * a.Ls);
+        __syncthreads();
+#pragma unroll
+        for (int d = 0; d < 8; ++d) {
+            compute_stage_rt<P, DAG>(st[d % DEPTH], d, rec + d * LB, acc);
+            if (d + DEPTH < 8) load_stage<P>(a, s, nb[d + DEPTH], st[d % DEPTH]);
+        }
+        return;
+    }
     if constexpr (P == P64) {   // links and neighbour indices already staged by the caller
         const int* nbl = reinterpret_cast<const int*>(lds + (size_t)a.NS * 8 * LB) + sl * 8;
         const unsigned char* lr = lds + sl * 8 * LB;
@@ -417,7 +451,7 @@ __device__ __forceinline__ void hop_all(const HopArgs& a, int lb, unsigned char*
     int nb[8];
 #pragma unroll
     for (int d = 0; d < 8; ++d) nb[d] = a.nbr[(size_t)d * a.Vh + site];
-    if constexpr (!DENSE) stage_links<P>(a, site, sl, s, lds);   // before the gathers: nothing to wait behind
+    if constexpr (!DENSE) stage_links<P>(a, site, sl, s, lds, s);   // before the gathers: nothing to wait behind
     Stage<P> st[DEPTH];
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) load_stage<P>(a, s, nb[d], st[d]);
@@ -840,14 +874,15 @@ __device__ __forceinline__ void hop_all_mfma(const HopArgs& a, int lb, unsigned 
     for (int d = 0; d < 8; ++d) nb[d] = a.nbr[(size_t)d * a.Vh + site];
     // the links first, written to LDS after the gathers are issued (as in
     // hop_blk_mfma)
-    LinkPre<P, 1> pre;
-    links_load_site<P>(a, site, s, pre);
+    constexpr int K = DEPTH > 4 ? 8 : 4;   // link rows in flight
+    LinkPre<P, 1, K> pre;
+    links_load_site<P, K>(a, site, s, pre);
     __builtin_amdgcn_sched_barrier(0);
     MStage st[DEPTH];
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) load_mstage<P>(a, s, nb[d], st[d], true);
     __builtin_amdgcn_sched_barrier(0);
-    links_put_site<P>(a, site, sl, s, pre, lds);
+    links_put_site<P, K>(a, site, sl, s, pre, lds);
     __syncthreads();
     const unsigned char* lr = lds + sl * 8 * LB;
 #pragma unroll
@@ -1157,13 +1192,17 @@ __device__ __forceinline__ double block_sum(double x, double* red) {
 // the natural layout and the result written to it, through the epilogue's
 // tile.  At 24^3x64, Ls = 24 the hop takes 1.90 ms instead of 1.74 ms plus its
 // share of two layout passes (2.26 ms); dwf_apply 9.55 -> 5.32 ms.
-template <int P, bool DAG, bool HOP, int MF, bool DENSE = false, bool BLK = false, bool NAT = false>
-__global__ void __launch_bounds__(256, (MF == 3 && P == P16 && !DENSE) ? 5 : 3) k_hop(const HopArgs a) {
+// LAT (per-site hops of small grids): nothing hides a wavefront's latency, so
+// every operand is requested up front -- links, 8 (FP64: 4) neighbours, aux
+// fields -- at a register budget of one or two wavefronts per SIMD, and the
+// column sweeps load whole batches.
+template <int P, bool DAG, bool HOP, int MF, bool DENSE = false, bool BLK = false, bool NAT = false, bool LAT = false>
+__global__ void __launch_bounds__(256, LAT ? (P == P64 || P == P32 ? 1 : 2) : (MF == 3 && P == P16 && !DENSE) ? 5 : 3) k_hop(const HopArgs a) {
     using A = typename PT<P>::A;
     // (FP64 would spill more: its reductions stay launches of their own)
     constexpr bool RED = P != P64 && DAG && HOP && !DENSE;
     // column-sweep load batch: what each variant's register budget allows
-    constexpr int COLB = P == P64 ? 1 : (P == P16 && MF) ? 4 : 8;
+    constexpr int COLB = LAT ? 8 : P == P64 ? 1 : (P == P16 && MF) ? 4 : 8;
     extern __shared__ unsigned char smem_raw[];
     A* lds = reinterpret_cast<A*>(smem_raw);
     __shared__ double red[16];
@@ -1197,23 +1236,37 @@ __global__ void __launch_bounds__(256, (MF == 3 && P == P16 && !DENSE) ? 5 : 3) 
                              : NO_ROW;
     }
 
+    // LAT: the streamed operands are requested before the hop (inactive work-items read site 0)
+    RawSpinor<P> raw1, raw2;
+    if constexpr (LAT) {
+        if (a.aux) raw1.load(a.aux, a.aux_nrm, a.N, active ? n : 0);
+        if (a.aux2) raw2.load(a.aux2, a.aux2_nrm, a.N, active ? n : 0);
+    }
+    auto load_op = [&](const void* f, const float* nrm, const RawSpinor<P>& raw, A (&x)[24]) __attribute__((always_inline)) {
+        if constexpr (LAT) raw.get(x);
+        else if (active) ld_spinor<P, true>(f, nrm, a.N, n, x);
+        if (!active) {
+#pragma unroll
+            for (int k = 0; k < 24; ++k) x[k] = 0;
+        }
+    };
     A v[24];
 #pragma unroll
     for (int k = 0; k < 24; ++k) v[k] = 0;
     if (HOP) {
         // every work-item takes part (staging barrier; the MFMA needs the
         // whole wave); padding work-items read site 0 and discard it
-        if constexpr (P == P64 && !BLK) {
+        if constexpr (P == P64 && !BLK && !LAT) {
             if constexpr (DENSE) stage_links_tbl<P>(a, lb, smem_raw);
-            else stage_links<P>(a, active ? site : 0, sl, s, smem_raw);
+            else stage_links<P>(a, active ? site : 0, sl, s, smem_raw, s);
             __syncthreads();
         }
         if constexpr (MF && BLK) hop_blk_mfma<P, DAG>(a, lb, smem_raw, sl, s, tid & 3, v);
-        else if constexpr (MF) hop_all_mfma<P, DAG, MF>(a, lb, smem_raw, active ? site : 0, sl, s, tid & 3, v);
+        else if constexpr (MF) hop_all_mfma<P, DAG, LAT ? 8 : MF>(a, lb, smem_raw, active ? site : 0, sl, s, tid & 3, v);
         else if constexpr (BLK && P == P64) hop_blk_f64<DAG>(a, lb, smem_raw, sl, s, v);
         else if constexpr (BLK) hop_blk_vec<P, DAG>(a, lb, smem_raw, sl, s, v);
-        else if constexpr (P == P64) { if (active) hop_all<P, DAG, DENSE>(a, lb, smem_raw, site, sl, s, v); }
-        else hop_all<P, DAG, DENSE>(a, lb, smem_raw, active ? site : 0, sl, s, v);
+        else if constexpr (P == P64 && !LAT) { if (active) hop_all<P, DAG, DENSE, false>(a, lb, smem_raw, site, sl, s, v); }
+        else hop_all<P, DAG, DENSE, LAT>(a, lb, smem_raw, active ? site : 0, sl, s, v);
         if (!active) {
 #pragma unroll
             for (int k = 0; k < 24; ++k) v[k] = 0;
@@ -1262,11 +1315,7 @@ __global__ void __launch_bounds__(256, (MF == 3 && P == P16 && !DENSE) ? 5 : 3) 
         bool aux2_done = false;
         if (a.aux2 && a.opA.kind == 0) {   // fold cr * aux2 in before the 5D ops (A = 1)
             A x[24];
-            if (active) ld_spinor<P, true>(a.aux2, a.aux2_nrm, a.N, n, x);
-            else {
-#pragma unroll
-                for (int k = 0; k < 24; ++k) x[k] = 0;
-            }
+            load_op(a.aux2, a.aux2_nrm, raw2, x);
             const A cr = (A)a.cr;
 #pragma unroll
             for (int k = 0; k < 24; ++k) v[k] = fmadd(ch, v[k], cr * x[k]);
@@ -1292,11 +1341,7 @@ __global__ void __launch_bounds__(256, (MF == 3 && P == P16 && !DENSE) ? 5 : 3) 
             __syncthreads();
         } else if (a.aux) {
             A x[24];
-            if (active) ld_spinor<P, true>(a.aux, a.aux_nrm, a.N, n, x);
-            else {
-#pragma unroll
-                for (int k = 0; k < 24; ++k) x[k] = 0;
-            }
+            load_op(a.aux, a.aux_nrm, raw1, x);
             const A ca = (A)(a.ca * alpha);
             if (a.opB2.kind != 0) {
                 column_phase<COLB>(lds, tid, sl, s, Ls, x, a.opB, ca, a.opB2, mp, mm);
@@ -1317,7 +1362,7 @@ __global__ void __launch_bounds__(256, (MF == 3 && P == P16 && !DENSE) ? 5 : 3) 
         }
         if (a.aux2 && !aux2_done && active) {
             A x[24];
-            ld_spinor<P, true>(a.aux2, a.aux2_nrm, a.N, n, x);
+            load_op(a.aux2, a.aux2_nrm, raw2, x);
             const A cr = (A)a.cr;
 #pragma unroll
             for (int k = 0; k < 24; ++k) v[k] = fmadd(cr, x[k], v[k]);
@@ -1590,6 +1635,10 @@ static hipError_t launch_hop_t(const HopArgs& a, int nblk, hipStream_t st) {
     if constexpr ((P == P16 || P == PB16) && HOP) {
         if (a.frag) {
             const size_t shm = std::max(tile, stage_bytes(LinkLds<P, 1>::LB, a.NS) + (a.blk ? share_bytes(P, true, NT) : 0));
+            if (a.lat) {
+                hipLaunchKernelGGL((k_hop<P, DAG, HOP, 3, false, false, false, true>), dim3(nblk), dim3(NT), shm, st, a);
+                return hipGetLastError();
+            }
             if (a.blk) {   // the block path keeps its own loads in flight
                 hipLaunchKernelGGL((k_hop<P, DAG, HOP, 3, false, true>), dim3(nblk), dim3(NT), shm, st, a);
                 return hipGetLastError();
@@ -1605,7 +1654,8 @@ static hipError_t launch_hop_t(const HopArgs& a, int nblk, hipStream_t st) {
             const size_t links = a.blk ? (size_t)(2 * a.NS + 1) * LinkLds<P, 0>::LB + share_bytes(P, false, NT)
                                        : stage_bytes(LinkLds<P, 0>::LB, a.NS);
             const size_t shm = std::max((size_t)STR * NT * sizeof(A), links);
-            if (a.blk) hipLaunchKernelGGL((k_hop<P, DAG, HOP, 0, false, true, true>), dim3(nblk), dim3(NT), shm, st, a);
+            if (a.lat) hipLaunchKernelGGL((k_hop<P, DAG, HOP, 0, false, false, true, true>), dim3(nblk), dim3(NT), shm, st, a);
+            else if (a.blk) hipLaunchKernelGGL((k_hop<P, DAG, HOP, 0, false, true, true>), dim3(nblk), dim3(NT), shm, st, a);
             else hipLaunchKernelGGL((k_hop<P, DAG, HOP, 0, false, false, true>), dim3(nblk), dim3(NT), shm, st, a);
             return hipGetLastError();
         }
@@ -1620,6 +1670,12 @@ static hipError_t launch_hop_t(const HopArgs& a, int nblk, hipStream_t st) {
         }
     }
     const size_t shm = HOP ? std::max(tile, stage_bytes(LinkLds<P, 0>::LB, a.NS)) : tile;
+    if constexpr (HOP) {
+        if (a.lat) {
+            hipLaunchKernelGGL((k_hop<P, DAG, HOP, 0, false, false, false, true>), dim3(nblk), dim3(NT), shm, st, a);
+            return hipGetLastError();
+        }
+    }
     hipLaunchKernelGGL((k_hop<P, DAG, HOP, 0>), dim3(nblk), dim3(NT), shm, st, a);
     return hipGetLastError();
 }

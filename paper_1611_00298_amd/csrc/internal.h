@@ -164,6 +164,37 @@ __device__ __forceinline__ void st_spinor(void* __restrict__ base, float* __rest
     }
 }
 
+// One spinor's stored words, loaded now and converted later.
+template <int P> struct RawSpinor {
+    u32x4_t w[PT<P>::NB];
+    float nrm;
+    __device__ __forceinline__ void load(const void* __restrict__ base, const float* __restrict__ norms, size_t N,
+                                         size_t n) {
+        const uint32_t off = (uint32_t)n * 16u;
+#pragma unroll
+        for (int b = 0; b < PT<P>::NB; ++b) w[b] = at<u32x4_t>(base, b * N * 16, off);
+        nrm = P == P16 ? norms[n] : 1.0f;
+    }
+    __device__ __forceinline__ void get(typename PT<P>::A (&v)[24]) const {
+#pragma unroll
+        for (int b = 0; b < PT<P>::NB; ++b) {
+            if constexpr (P == P64) {
+                const double2 t = __builtin_bit_cast(double2, w[b]);
+                v[2 * b] = t.x; v[2 * b + 1] = t.y;
+            } else if constexpr (P == P32) {
+                const float4 t = __builtin_bit_cast(float4, w[b]);
+                v[4 * b] = t.x; v[4 * b + 1] = t.y; v[4 * b + 2] = t.z; v[4 * b + 3] = t.w;
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    v[8 * b + 2 * q] = P == P16 ? h2f(w[b][q] & 0xffffu) * nrm : b2f(w[b][q] & 0xffffu);
+                    v[8 * b + 2 * q + 1] = P == P16 ? h2f(w[b][q] >> 16) * nrm : b2f(w[b][q] >> 16);
+                }
+            }
+        }
+    }
+};
+
 // Raw 16-bit spinor load: the stored values without the FP16 site norm
 // (returned separately, 1 for BF16), so that the norm can be applied after
 // the spin projection on 12 instead of 24 numbers.
@@ -320,6 +351,7 @@ struct HopArgs {
     const int* nbrb;     // with blk: neighbours of the table's blocks, [block][k][slot] (k = 0: x inside, 1-4: outside)
     const void* lnkb;    // with blk: the links in block-major order, [block][d][slot] records (FP32 or compact 16-bit)
     int Vh, Ls, NS;
+    int lat;             // the latency form: all operands in flight at once (grids that do not fill the GPU)
     size_t N;
     double mp, mm;
     Op5 opA, opB, opC;
