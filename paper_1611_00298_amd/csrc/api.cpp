@@ -33,8 +33,8 @@ hipError_t launch_pupdate(int prec, const void* z, const float* zn, const void* 
                           int npart, const RedOut& ro, int Vh, int Ls, int NS, size_t N, double b5, double c5, double mp, double mm,
                           int nblk, hipStream_t st);
 hipError_t launch_r_update(int prec, void* r, float* rn, const void* w, const float* wn, double* sc,
-                           int i_num, int i_den, int i_save, size_t n5, size_t N, double* partial,
-                           int nblk, hipStream_t st);
+                           int i_num, int i_den, int i_save, const double* part, int npart, size_t n5, size_t N,
+                           double* partial, int nblk, hipStream_t st);
 hipError_t launch_x_batch(int prec, void* x, float* xn, const void* const* p, const float* const* pn,
                           const int* slots, int cnt, const double* sc, size_t n5, size_t N, int nblk,
                           hipStream_t st);
@@ -318,8 +318,11 @@ struct HopCall {
     const void* aux_nat = nullptr;
     void* out_nat = nullptr;
     bool zero_pair = false;
-    // daggered hops below FP64: also sum the red_n partials of an earlier launch into scalar slot red_slot
+    // daggered hops below FP64 or in the latency form: also sum the red_n partials of an earlier
+    // launch into scalar slot red_slot (and host memory)
     int red_n = 0, red_slot = 0;
+    double* red_host = nullptr;
+    const double* red_in = nullptr;
 };
 
 void run_hop(eofa_ctx* c, const HopCall& h) {
@@ -400,10 +403,9 @@ void run_hop(eofa_ctx* c, const HopCall& h) {
     }
     if (h.red_n) {
         if (h.partial) fail(EOFA_EDEVICE, "internal: a hop cannot reduce the partials it writes");
-        a.red_in = c->partial;
+        a.red_in = h.red_in;
         a.red_n = h.red_n;
-        a.red_slot = h.red_slot;
-        a.dsc_red = c->sc;
+        a.red = RedOut{c->sc, h.red_slot, h.red_host, h.red_slot, 1};
     }
     // bookkeeping: flops (fixed convention) and algorithmic bytes
     double f = 0, nfields = 1;
@@ -528,9 +530,9 @@ void schur_k2_tilde(eofa_ctx* c, int prec, const Half& tmp, const Half& pt, Half
 }
 // K3: tmp_e = M_ee^-dag Dtilde^dag Dh^dag_eo in_o   (red_n > 0: and the sum of K2's partials into red_slot)
 void schur_k3(eofa_ctx* c, int prec, const Half& in, Half& tmp, double mp, double mm, int red_n = 0,
-              int red_slot = 0) {
+              int red_slot = 0, double* red_host = nullptr, const double* red_in = nullptr) {
     HopCall h;
-    h.red_n = red_n; h.red_slot = red_slot;
+    h.red_n = red_n; h.red_slot = red_slot; h.red_host = red_host; h.red_in = red_in ? red_in : c->partial;
     h.prec = prec; h.dag = true; h.par = 0; h.in = &in; h.out = &tmp;
     h.A = Dt(c, 1); h.C = MeeInv(c, 1); h.mp = mp; h.mm = mm;
     run_hop(c, h);
@@ -657,6 +659,9 @@ SolveResult cgnr_schur(eofa_ctx* c, double mp, double mm, const Half& bhat, Half
         c->flops += 48.0 * cnt * (double)c->n5;
         pending0 = k + 1;
     };
+    // which sums ride in other launches: |w|^2 (FP64: |r|^2) in K3, |z|^2
+    // (FP64: |w|^2 too) in the update that needs it
+    const bool in_k3 = prec != P64 || c->small_grid, in_p = nb <= PUPD_PARTIALS;
     int cur = S_ZZ0, nxt = S_ZZ1;
     // z = Mhat^dag r ; p_0 = z ; pt = Dtilde p_0 (mixed: the ring holds Dtilde p)
     schur_k3(c, prec, r, tmp, mp, mm);
@@ -683,9 +688,6 @@ SolveResult cgnr_schur(eofa_ctx* c, double mp, double mm, const Half& bhat, Half
         // The scalars of iteration k go to the host ring after its K4
         // and are read while iteration k+1 runs, so the host never waits on an
         // idle GPU; decisions therefore use the estimate one iteration late.
-        // |z|^2 of at most PUPD_PARTIALS partials is summed by the direction
-        // update itself; more than that by a reduction of its own.
-        const bool in_p = nb <= PUPD_PARTIALS;
         double rr_est = rr;
         int pend_cur = -1;          // slot of |z_k|^2 of the pending ring entry, -1: none
         // Stagnation guard: in 16-bit arithmetic the recursion can stall
@@ -703,8 +705,8 @@ SolveResult cgnr_schur(eofa_ctx* c, double mp, double mm, const Half& bhat, Half
             Half& p = *pr[k % XBATCH];
             schur_k1(c, prec, p, tmp, mp, mm);
             schur_k2_tilde(c, prec, tmp, p, w, mp, mm, c->partial);
-            if (prec == P64) reduce(c, nb, S_WW);
-            schur_k3(c, prec, w, tmp, mp, mm, prec == P64 ? 0 : nb, S_WW);   // and |w|^2 from K2's partials
+            if (!in_k3) reduce(c, nb, S_WW);
+            schur_k3(c, prec, w, tmp, mp, mm, in_k3 ? nb : 0, S_WW);   // and |w|^2 from K2's partials
             schur_k4_update(c, prec, tmp, w, z, mp, mm, cur, S_WW, S_ALPHA + k % XBATCH, c->partial);
             res.iters++;
             double* slot_k = c->ring + 4 * (k & 1);
@@ -769,39 +771,52 @@ SolveResult cgnr_schur(eofa_ctx* c, double mp, double mm, const Half& bhat, Half
         if (!res.converged) fold_x();
         return res;
     }
-    // FP64: plain CGNR with the recursively updated residual r
+    // FP64: plain CGNR with the recursively updated residual r.  The host
+    // reads |r|^2 of iteration k after it has queued the rest of that
+    // iteration, so that the GPU does not wait for it; at convergence that
+    // rest (the next direction) is left unused.
     Half& pt = *ptp;
     while (res.iters < maxiter) {
         Half& p = *pr[k % XBATCH];
         // w = Mhat p, |w|^2
         schur_k1(c, prec, pt, tmp, mp, mm);
         schur_k2(c, prec, tmp, p, w, mp, mm, c->partial);
-        reduce(c, nb, S_WW);
+        if (!in_p) reduce(c, nb, S_WW);
         // r -= alpha w, |r|^2 (alpha kept for the batched x update)
+        double* part_r = c->partial + nb;   // behind K2's partials
         {
             const int ev = timing_begin(c);
-            hipchk(launch_r_update(prec, r.d, r.nrm, w.d, w.nrm, c->sc, cur, S_WW, S_ALPHA + k % XBATCH,
-                                   c->n5, c->N, c->partial, c->nblk_blas, c->st), "r update");
+            hipchk(launch_r_update(prec, r.d, r.nrm, w.d, w.nrm, c->sc, cur, S_WW, S_ALPHA + k % XBATCH, c->partial,
+                                   in_p ? nb : 0, c->n5, c->N, part_r, c->nblk_blas, c->st), "r update");
             timing_end(c, ev, C_BLAS, (double)c->n5 * 3.0 * spinor_bytes(prec));
             c->flops += 48.0 * (double)c->n5;
         }
         res.iters++;
-        rr = reduce_read(c, c->nblk_blas, S_RR);
-        check_finite(rr, "residual norm");
-        if (std::sqrt(rr) <= thresh) {
-            flush(k);
-            res.converged = true;
-            break;
+        double* rr_k = c->ring + 4 * (k & 1);
+        const bool more = res.iters < maxiter;
+        if (!more || !in_k3) {
+            hipchk(launch_reduce(part_r, c->nblk_blas, RedOut{c->sc, S_RR, rr_k, S_RR, 1}, c->st), "reduce");
+            hipchk(hipEventRecord(c->ring_ev[k & 1], c->st), "hipEventRecord");
         }
         if (k - pending0 + 1 == XBATCH) flush(k);
-        if (res.iters >= maxiter) { flush(k); break; }
-        // z = Mhat^dag r, |z|^2 ; p_{k+1} = z + beta p_k ; pt = Dtilde p_{k+1}
-        schur_k3(c, prec, r, tmp, mp, mm);
-        schur_k4(c, prec, tmp, r, z, mp, mm, c->partial);
-        reduce(c, nb, nxt);
-        Half& pn1 = *pr[(k + 1) % XBATCH];
-        pupdate(c, prec, z, &p, pn1, &pt, nxt, cur, mp, mm);
-        c->flops += 72.0 * (double)c->n5 + 48.0 * (double)c->n5;
+        if (more) {
+            // z = Mhat^dag r, |z|^2 ; p_{k+1} = z + beta p_k ; pt = Dtilde p_{k+1}
+            schur_k3(c, prec, r, tmp, mp, mm, in_k3 ? c->nblk_blas : 0, S_RR, rr_k, part_r);
+            if (in_k3) hipchk(hipEventRecord(c->ring_ev[k & 1], c->st), "hipEventRecord");
+            schur_k4(c, prec, tmp, r, z, mp, mm, c->partial);
+            if (!in_p) reduce(c, nb, nxt);
+            Half& pn1 = *pr[(k + 1) % XBATCH];
+            pupdate(c, prec, z, &p, pn1, &pt, nxt, cur, mp, mm, in_p ? nb : 0);
+            c->flops += 72.0 * (double)c->n5 + 48.0 * (double)c->n5;
+        }
+        hipchk(hipEventSynchronize(c->ring_ev[k & 1]), "hipEventSynchronize");
+        rr = rr_k[0];
+        check_finite(rr, "residual norm");
+        if (std::sqrt(rr) <= thresh) res.converged = true;
+        if (res.converged || !more) {
+            flush(k);
+            break;
+        }
         std::swap(cur, nxt);
         ++k;
     }
@@ -1900,6 +1915,7 @@ int eofa_ctx_create(eofa_ctx_t** out, const eofa_geom_t* g, const void* U, void*
             c->nblk_hop = (c->Vh + c->NS - 1) / c->NS;
             c->nblk_blas = blas_blocks(c->n5);
             size_t np = (size_t)2 * c->nblk_hop;
+            np = std::max(np, (size_t)c->nblk_hop + c->nblk_blas);
             np = std::max(np, (size_t)action_blocks(c->V));
             np = std::max(np, (size_t)md_blocks(4 * c->V));
             np = std::max(np, (size_t)gauge_action_blocks(c->V));

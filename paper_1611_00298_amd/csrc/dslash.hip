@@ -1199,8 +1199,8 @@ __device__ __forceinline__ double block_sum(double x, double* red) {
 template <int P, bool DAG, bool HOP, int MF, bool DENSE = false, bool BLK = false, bool NAT = false, bool LAT = false>
 __global__ void __launch_bounds__(256, LAT ? (P == P64 || P == P32 ? 1 : 2) : (MF == 3 && P == P16 && !DENSE) ? 5 : 3) k_hop(const HopArgs a) {
     using A = typename PT<P>::A;
-    // (FP64 would spill more: its reductions stay launches of their own)
-    constexpr bool RED = P != P64 && DAG && HOP && !DENSE;
+    // (the FP64 throughput forms would spill more: their reductions stay launches of their own)
+    constexpr bool RED = (P != P64 || LAT) && DAG && HOP && !DENSE && !NAT;
     // column-sweep load batch: what each variant's register budget allows
     constexpr int COLB = LAT ? 8 : P == P64 ? 1 : (P == P16 && MF) ? 4 : 8;
     extern __shared__ unsigned char smem_raw[];
@@ -1216,7 +1216,7 @@ __global__ void __launch_bounds__(256, LAT ? (P == P64 || P == P32 ? 1 : 2) : (M
         if (a.red_n) {   // the first workgroup reduces, the others are the hop's
             if (blk == 0) {
                 const double t = sum_partials(a.red_in, a.red_n, red);
-                if (tid == 0) a.dsc_red[a.red_slot] = t;
+                if (tid == 0) red_store(a.red, t);
                 return;
             }
             --blk;
@@ -1412,8 +1412,8 @@ __global__ void __launch_bounds__(256, LAT ? (P == P64 || P == P32 ? 1 : 2) : (M
 // Schur application:  p <- z + beta p  (beta = sc[i1]/sc[i0], or p <- z on
 // the first call), pt <- Dtilde p = (b5 + c5 L) p.  With pt == nullptr only
 // the Cayley-transformed direction is kept: p <- Dtilde z + beta p.
-// npart > 0 (that form only): sc[i_new] is still in its npart partials; every
-// workgroup sums them, the first one stores the result through `ro`.
+// npart > 0: sc[i_new] is still in its npart partials; every workgroup sums
+// them, the first one stores the result through `ro`.
 // ---------------------------------------------------------------------------
 template <int P>
 __global__ void __launch_bounds__(256) k_pupdate(const void* z, const float* z_nrm, const void* pold,
@@ -1434,17 +1434,17 @@ __global__ void __launch_bounds__(256) k_pupdate(const void* z, const float* z_n
     A v[24];
 #pragma unroll
     for (int k = 0; k < 24; ++k) v[k] = 0;
+    if (active) ld_spinor<P>(z, z_nrm, N, n, v);
+    double znew = 0;
+    if (npart) {
+        __shared__ double red[16];
+        znew = sum_partials(part, npart, red);
+        if (blockIdx.x == 0 && tid == 0) red_store(ro, znew);
+    } else if (!first) {
+        znew = sc[i_new];
+    }
     if (!pt) {
         // search directions kept as pt = Dtilde p:  pt <- Dtilde z + beta pt_old
-        if (active) ld_spinor<P>(z, z_nrm, N, n, v);
-        double znew = 0;
-        if (npart) {
-            __shared__ double red[16];
-            znew = sum_partials(part, npart, red);
-            if (blockIdx.x == 0 && tid == 0) red_store(ro, znew);
-        } else if (!first) {
-            znew = sc[i_new];
-        }
         put_row(lds, tid, v);
         __syncthreads();
         A t[24];
@@ -1462,9 +1462,8 @@ __global__ void __launch_bounds__(256) k_pupdate(const void* z, const float* z_n
         return;
     }
     if (active) {
-        ld_spinor<P>(z, z_nrm, N, n, v);
         if (!first) {
-            const A beta = (A)(sc[i_new] / sc[i_old]);
+            const A beta = (A)(znew / sc[i_old]);
             A q[24];
             ld_spinor<P>(pold, pold_nrm, N, n, q);
 #pragma unroll
@@ -1625,7 +1624,7 @@ template <int P, bool DAG, bool HOP>
 static hipError_t launch_hop_t(const HopArgs& a, int nblk, hipStream_t st) {
     using A = typename PT<P>::A;
     if (a.red_n) {
-        if (P == P64 || !DAG || !HOP) return hipErrorInvalidValue;
+        if ((P == P64 && !a.lat) || !DAG || !HOP || a.out_nat) return hipErrorInvalidValue;
         ++nblk;
     }
     const int NT = a.NS * a.Ls;

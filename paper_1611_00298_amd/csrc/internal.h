@@ -362,11 +362,11 @@ struct HopArgs {
     // dsc[s_num] / dsc[s_den], which is also stored to dsc[s_alpha] (>= 0)
     double* dsc;
     int s_num, s_den, s_alpha;
-    // with red_n > 0 (daggered hops below FP64) the launch has one workgroup more, which sums the
-    // red_n partials an earlier launch left into dsc_red[red_slot]
+    // with red_n > 0 (daggered hops below FP64 or in the latency form) the launch has one
+    // workgroup more, which sums the red_n partials an earlier launch left
     const double* red_in;
-    int red_n, red_slot;
-    double* dsc_red;
+    int red_n;
+    RedOut red;
     // dense 5D blocks of D_EOFA's even-odd form (the dense comparison path, FP64, FP32 or FP16):
     // [D5+, D5-, D5inv+, D5inv-], each Ls x Ls row major; an Op5 of kind 3
     // applies D5 (a = 0) or D5^-1 (a = 1), transposed when tr != 0
