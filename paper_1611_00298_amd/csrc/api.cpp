@@ -1896,17 +1896,20 @@ int eofa_ctx_create(eofa_ctx_t** out, const eofa_geom_t* g, const void* U, void*
             c->NS = best;
             int blocks_env = 1;
             if (const char* e = getenv("EOFA_BLOCKS")) blocks_env = atoi(e);   // tuning: 0 per-site, 2 block-sharing hops on any grid
-            // Small lattices (at most one wavefront per SIMD): the hop is bound
+            // Small lattices (at most two wavefronts per SIMD): the hop is bound
             // by its chain of dependent accesses, not by throughput, so the
             // workgroups shrink to one wavefront, which spreads the links and
             // barriers over more CUs, and the hop takes its latency form.  FP64
             // solve on 4^4, Ls = 8: 18.2 -> 16.4 ms over the latency form alone
             // (20.6 ms without); 8^3x16, Ls = 8 (512 wavefronts): a trajectory
-            // 182 -> 172 ms (202 ms).  Beyond it other wavefronts hide the
-            // latency: 1440 wavefronts 74.6 against 75.9 ms in the latency form,
-            // 3888 472 against 495 ms.
+            // 182 -> 172 ms (202 ms); 12x10x8x18, Ls = 10 (1440): FP32 solve 74.2 ->
+            // 68.2 ms.  Where whole sites fill less than 52 of a wavefront's lanes
+            // (Ls = 24: 48) the line is at one wavefront per SIMD: 8^3x16, Ls = 24
+            // (2048) 69.0 against 73.6 ms.  Beyond it other wavefronts hide the
+            // latency: 12^3x24, Ls = 12 (4148) 472 against 495 ms.
             const int ns1 = std::max(1, 64 / c->Ls);
-            c->small_grid = blocks_env == 1 && (long)((c->Vh + ns1 - 1) / ns1) * ((ns1 * c->Ls + 63) / 64) <= 1024;
+            const long waves = (long)((c->Vh + ns1 - 1) / ns1) * ((ns1 * c->Ls + 63) / 64);
+            c->small_grid = blocks_env == 1 && waves <= (ns1 * c->Ls >= 52 ? 2048 : 1024);
             if (c->small_grid) c->NS = ns1;
             if (const char* e = getenv("EOFA_NS")) {   // tuning override: sites per workgroup
                 const int q = atoi(e);

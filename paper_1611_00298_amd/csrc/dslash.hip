@@ -399,14 +399,14 @@ __device__ __forceinline__ void compute_stage_rt(const Stage<P>& st, int d, cons
 // registers allow no more), links from LDS.  Every work-item of the
 // workgroup must call this (it contains the staging barrier); padding
 // work-items pass site 0 and discard the result.
-// LAT (grids that leave the GPU mostly idle): the links' and then 8 (FP64: 4)
-// neighbour spinors' loads are all issued before anything waits.
+// LAT (grids that leave the GPU mostly idle): the links' and then 8 (FP32: 5,
+// FP64: 4) neighbour spinors' loads are all issued before anything waits.
 template <int P, bool DAG, bool DENSE, bool LAT>
 __device__ __forceinline__ void hop_all(const HopArgs& a, int lb, unsigned char* lds, int site, int sl, int s,
                                         typename PT<P>::A (&acc)[24]) {
     constexpr int LB = LinkLds<P, 0>::LB;
     if constexpr (LAT) {
-        constexpr int DEPTH = P == P64 ? 4 : 8, K = 9;   // 9 link elements per work-item at Ls = 8
+        constexpr int DEPTH = P == P64 ? 4 : P == P32 ? 5 : 8, K = 9;   // 9 link elements per work-item at Ls = 8
         using T = typename std::conditional<P == P64, d2v, f2v>::type;
         int nb[8];
 #pragma unroll
@@ -1193,11 +1193,11 @@ __device__ __forceinline__ double block_sum(double x, double* red) {
 // tile.  At 24^3x64, Ls = 24 the hop takes 1.90 ms instead of 1.74 ms plus its
 // share of two layout passes (2.26 ms); dwf_apply 9.55 -> 5.32 ms.
 // LAT (per-site hops of small grids): nothing hides a wavefront's latency, so
-// every operand is requested up front -- links, 8 (FP64: 4) neighbours, aux
-// fields -- at a register budget of one or two wavefronts per SIMD, and the
-// column sweeps load whole batches.
+// every operand is requested up front -- links, 8 (FP32: 5, FP64: 4)
+// neighbours, aux fields -- at a register budget of two wavefronts per SIMD
+// (FP64: one), and the column sweeps load whole batches.
 template <int P, bool DAG, bool HOP, int MF, bool DENSE = false, bool BLK = false, bool NAT = false, bool LAT = false>
-__global__ void __launch_bounds__(256, LAT ? (P == P64 || P == P32 ? 1 : 2) : (MF == 3 && P == P16 && !DENSE) ? 5 : 3) k_hop(const HopArgs a) {
+__global__ void __launch_bounds__(256, LAT ? (P == P64 ? 1 : 2) : (MF == 3 && P == P16 && !DENSE) ? 5 : 3) k_hop(const HopArgs a) {
     using A = typename PT<P>::A;
     // (the FP64 throughput forms would spill more: their reductions stay launches of their own)
     constexpr bool RED = (P != P64 || LAT) && DAG && HOP && !DENSE && !NAT;

@@ -37,9 +37,9 @@ def test_hop_forms(Ls, form, monkeypatch):
     _check((4, 2, 6, 4), Ls, ("fp64", "fp32", "fp16", "bf16"))
 
 
-@pytest.mark.parametrize("L,Ls", [((8, 8, 4, 32), 16), ((8, 8, 4, 34), 16), ((6, 6, 10, 16), 24)])
+@pytest.mark.parametrize("L,Ls", [((8, 8, 8, 32), 16), ((8, 8, 8, 34), 16), ((8, 8, 4, 16), 24), ((8, 8, 4, 18), 24)])
 def test_grid_size_line(L, Ls):
-    """1024 wavefronts, just above, and a block-sharing grid."""
+    """2048 wavefronts of full lanes and 1024 of 48, and just above each."""
     _check(L, Ls, ("fp64", "fp16"))
 
 
