@@ -318,6 +318,7 @@ struct HopCall {
     const void* aux_nat = nullptr;
     void* out_nat = nullptr;
     bool zero_pair = false;
+    const Half* in_p1 = nullptr;   // small grids: parity 1 runs in the same launch (par = 0), from this input
     // daggered hops below FP64 or in the latency form: also sum the red_n partials of an earlier
     // launch into scalar slot red_slot (and host memory)
     int red_n = 0, red_slot = 0;
@@ -344,6 +345,12 @@ void run_hop(eofa_ctx* c, const HopCall& h) {
     a.aux_nat = h.aux_nat;
     a.out_nat = h.out_nat;
     a.zero_pair = h.zero_pair;
+    if (h.in_p1) {
+        if (!h.out_nat || h.par != 0 || !c->small_grid) fail(EOFA_EDEVICE, "internal: unsupported two-parity hop");
+        a.in_p1 = h.in_p1->d;
+        a.gauge_p1 = (size_t)8 * 9 * c->Vh * complex_bytes(P64);
+        a.nbr_p1 = (size_t)8 * c->Vh * sizeof(int);
+    }
     for (int mu = 0; mu < 4; ++mu) a.L[mu] = c->L[mu];
     a.out = h.out ? h.out->d : nullptr;
     a.out_nrm = h.out ? h.out->nrm : nullptr;
@@ -414,12 +421,13 @@ void run_hop(eofa_ctx* c, const HopCall& h) {
         f += op_flops(h.B, c->Ls) + op_flops(h.B2, c->Ls) + (h.hop ? 24.0 : 0.0), nfields += h.zero_pair ? 2 : 1;
     if (h.aux2) f += 24.0, nfields += 1;
     f += op_flops(h.C, c->Ls);
+    if (h.in_p1) f *= 2, nfields *= 2;
     c->flops += f * (double)c->n5;
     double bytes = nfields * spinor_bytes(h.prec) * (double)c->n5;
     // algorithmic link bytes: the 4V links of one checkerboard hop, 9 complex
     // numbers each at the field precision (what the kernel reads can be more:
     // FP32 links or the FP16 rows of the matrix-core path)
-    if (h.hop) bytes += 72.0 * complex_bytes(h.prec) * c->Vh;
+    if (h.hop) bytes += (h.in_p1 ? 2 : 1) * 72.0 * complex_bytes(h.prec) * c->Vh;
     const int ev = timing_begin(c);
     if (h.dmat) {
         if ((h.prec != P64 && h.prec != P32 && h.prec != P16) || h.C.kind != 0 || h.B2.kind != 0 || h.dev_alpha)
@@ -2007,8 +2015,9 @@ int dwf_apply(eofa_ctx_t* c, double mp, double mm, int dagger, int eo, eofa_prec
             // FP64: the hop's input goes to the device layout (already Dtilde in
             // where the hop needs that); the hop that ends the operator reads
             // the diagonal term's operand from `in` and writes `out` itself
-            auto final_hop = [&](const Half& x, int par, double ch) {
+            auto final_hop = [&](const Half& x, int par, double ch, const Half* x1 = nullptr) {
                 HopCall h;
+                h.in_p1 = x1;
                 h.prec = P; h.dag = dagger != 0; h.par = par; h.mp = mp; h.mm = mm;
                 h.in = &x; h.ch = ch; h.ca = 1.0;
                 h.A = dagger ? Dt(c, 1) : I5;
@@ -2021,8 +2030,9 @@ int dwf_apply(eofa_ctx_t* c, double mp, double mm, int dagger, int eo, eofa_prec
             Half& te = ws(c, "ap_t_e", P);
             from_natural(c, in, eo ? nullptr : &te, &to, pre, mp, mm);
             if (eo == 0) {
-                final_hop(to, 0, 1.0);   // out_p = M_ee in_p + Dh (Dtilde in)_pbar, or its adjoint
-                final_hop(te, 1, 1.0);
+                // out_p = M_ee in_p + Dh (Dtilde in)_pbar, or its adjoint
+                final_hop(to, 0, 1.0, c->small_grid ? &te : nullptr);
+                if (!c->small_grid) final_hop(te, 1, 1.0);
             } else {
                 if (dagger) schur_k3(c, P, to, te, mp, mm);
                 else schur_k1(c, P, to, te, mp, mm);

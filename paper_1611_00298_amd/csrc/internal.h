@@ -379,6 +379,10 @@ struct HopArgs {
     void* out_nat;
     int zero_pair;
     int L[4];
+    // latency form: both output parities in one launch of twice the workgroups; parity 1
+    // takes its input here and its links and neighbours this many bytes behind parity 0's
+    const void* in_p1;   // nullptr: one parity
+    size_t gauge_p1, nbr_p1;
 };
 
 // ---------------------------------------------------------------------------
