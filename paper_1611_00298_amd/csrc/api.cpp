@@ -39,13 +39,14 @@ hipError_t launch_x_batch(int prec, void* x, float* xn, const void* const* p, co
                           const int* slots, int cnt, const double* sc, size_t n5, size_t N, int nblk,
                           hipStream_t st);
 int blas_blocks(size_t n5);
+hipError_t launch_fold(int px, void* x, void* xl, void* xt, int Vh, int Ls, int NS, size_t N, double b5, double c5,
+                       double mp, double mm, int nblk, hipStream_t st);
 hipError_t launch_reduce(const double* partial, int n, const RedOut& ro, hipStream_t st);
 hipError_t launch_norm2(int prec, const void* f, const float* fn, size_t n5, size_t N,
                         double* partial, int nblk, hipStream_t st);
 hipError_t launch_convert(int pi, int po, const void* in, const float* inn, void* out, float* outn,
                           size_t n5, size_t N, int nblk, hipStream_t st);
-hipError_t launch_accum_hi(int px, void* xhi, void* xlo, float* xlon, size_t n5, size_t N, int nblk,
-                           hipStream_t st);
+hipError_t launch_accum_hi(void* xhi, void* xlo, size_t n5, size_t N, int nblk, hipStream_t st);
 hipError_t launch_zero(int prec, void* f, float* fn, size_t n5, size_t N, int nblk, hipStream_t st);
 hipError_t launch_ingest_gauge(const void* U, void* G, int* nbr, const int L[4], int Ls, int aperiodic,
                                hipStream_t st);
@@ -352,6 +353,10 @@ void run_hop(eofa_ctx* c, const HopCall& h) {
         a.nbr_p1 = (size_t)8 * c->Vh * sizeof(int);
     }
     for (int mu = 0; mu < 4; ++mu) a.L[mu] = c->L[mu];
+    if (h.out && h.out->prec != h.prec) {
+        if (h.prec != P64 || !h.hop || h.dag || h.dmat) fail(EOFA_EDEVICE, "internal: unsupported result precision");
+        a.out_prec = h.out->prec;
+    }
     a.out = h.out ? h.out->d : nullptr;
     a.out_nrm = h.out ? h.out->nrm : nullptr;
     a.aux = h.aux ? h.aux->d : nullptr;
@@ -607,15 +612,17 @@ SolveResult cgnr_schur(eofa_ctx* c, double mp, double mm, const Half& bhat, Half
                        double thresh, int maxiter, int prec, double delta, bool fused = false) {
     SolveResult res;
     const int nb = c->nblk_hop;
+    const bool mixed = prec != P64 || fused;
+    const int px = prec != P64 ? P32 : P64;
     Half& tmp64 = ws(c, "tmp_e", P64);
-    Half& r64 = ws(c, "r", P64);
     Half& xt64 = ws(c, "xt", P64);
-    // r = bhat - Mhat x
-    auto true_residual = [&](void) -> double {
+    Half& r = mixed ? ws(c, "r_lo", prec) : ws(c, "r", P64);
+    // r = bhat - Mhat x in FP64, stored in r's precision (xt64 holds Dtilde x if have_xt)
+    auto true_residual = [&](bool have_xt) -> double {
         HopCall h;
-        local_op(c, P64, x, xt64, Dt(c, 0), I5, mp, mm);
+        if (!have_xt) local_op(c, P64, x, xt64, Dt(c, 0), I5, mp, mm);
         schur_k1(c, P64, xt64, tmp64, mp, mm);
-        h.prec = P64; h.par = 1; h.in = &tmp64; h.out = &r64; h.ch = 1.0;
+        h.prec = P64; h.par = 1; h.in = &tmp64; h.out = &r; h.ch = 1.0;
         h.aux = &x; h.B = Mee(c, 0); h.ca = -1.0; h.aux2 = &bhat; h.cr = 1.0;
         h.mp = mp; h.mm = mm; h.partial = c->partial;
         run_hop(c, h);
@@ -623,18 +630,15 @@ SolveResult cgnr_schur(eofa_ctx* c, double mp, double mm, const Half& bhat, Half
     };
     double rr;
     if (guess) {
-        rr = true_residual();
+        rr = true_residual(false);
     } else {
         zero(c, x);
-        convert(c, bhat, r64);
-        rr = norm2(c, r64, S_RR);
+        convert(c, bhat, r);
+        rr = norm2(c, bhat, S_RR);
     }
     check_finite(rr, "residual norm");
     if (std::sqrt(rr) <= thresh) { res.converged = true; return res; }
 
-    const bool mixed = prec != P64 || fused;
-    const int px = prec != P64 ? P32 : P64;
-    Half& r = mixed ? ws(c, "r_lo", prec) : r64;
     Half& z = ws(c, "z", prec);
     Half* pr[XBATCH];   // ring of search directions p_k (buffer k mod XBATCH)
     for (int j = 0; j < XBATCH; ++j) pr[j] = &ws(c, "p" + std::to_string(j), prec);
@@ -642,10 +646,7 @@ SolveResult cgnr_schur(eofa_ctx* c, double mp, double mm, const Half& bhat, Half
     Half& w = ws(c, "w", prec);
     Half& tmp = ws(c, "tmp_lo_e", prec);
     Half& xl = mixed ? ws(c, "x_lo", px) : x;
-    if (mixed) {
-        convert(c, r64, r);
-        zero(c, xl);
-    }
+    if (mixed) zero(c, xl);
     // x += sum alpha_j p_j for the pending directions [pending0, k]
     int pending0 = 0;
     auto flush = [&](int k) {
@@ -683,9 +684,12 @@ SolveResult cgnr_schur(eofa_ctx* c, double mp, double mm, const Half& bhat, Half
         // K1 reads pt_k, K2 forms M_ee p_k = M_ee Dtilde^-1 pt_k in its
         // epilogue, and x_lo accumulates Dtilde x (undone before each
         // reliable update), which saves writing p next to pt.
-        auto fold_x = [&]() {
-            local_op(c, px, xl, xl, I5, DtInv(c, 0), mp, mm);
-            hipchk(launch_accum_hi(px, x.d, xl.d, xl.nrm, c->n5, c->N, c->nblk_blas, c->st), "accum");
+        auto fold_x = [&]() {   // x += Dtilde^-1 x_lo, x_lo = 0, xt64 = Dtilde x
+            const int ev = timing_begin(c);
+            hipchk(launch_fold(px, x.d, xl.d, xt64.d, c->Vh, c->Ls, c->NS, c->N, c->b5, c->c5, mp, mm, nb, c->st),
+                   "fold");
+            timing_end(c, ev, C_BLAS, (double)c->n5 * (3.0 * 192.0 + 2.0 * spinor_bytes(px)));
+            c->flops += (72.0 + 144.0) * (double)c->n5;
         };
         // Low-precision iterations keep z = Mhat^dag r by its own recursion
         // z <- z - alpha Mhat^dag w (folded into K4, so r is not stored);
@@ -740,7 +744,7 @@ SolveResult cgnr_schur(eofa_ctx* c, double mp, double mm, const Half& bhat, Half
                 // reliable update: fold the directions into x_lo, x_lo into x, recompute r in FP64
                 flush(k);
                 fold_x();
-                rr = true_residual();
+                rr = true_residual(true);
                 check_finite(rr, "true residual");
                 res.reliable++;
                 const double rprev = rmax;
@@ -762,7 +766,6 @@ SolveResult cgnr_schur(eofa_ctx* c, double mp, double mm, const Half& bhat, Half
                     res.stagnated = true;
                     break;
                 }
-                convert(c, r64, r);
                 schur_k3(c, prec, r, tmp, mp, mm);
                 schur_k4(c, prec, tmp, r, z, mp, mm, c->partial);
                 if (!in_p) reduce(c, nb, nxt);
@@ -1152,7 +1155,7 @@ DenseOut solve_dense(eofa_ctx* c, const double* dm, const Half& be, const Half& 
             dense_hop(c, dm, prec, true, 1, &t, o, I5, -1.0, &in, D5(1), 1.0, nullptr, 0.0, partial);
         };
         auto fold = [&]() {   // x_o += x_lo, x_lo = 0
-            hipchk(launch_accum_hi(P32, xo.d, xl.d, xl.nrm, c->n5, c->N, c->nblk_blas, c->st), "accum");
+            hipchk(launch_accum_hi(xo.d, xl.d, c->n5, c->N, c->nblk_blas, c->st), "accum");
         };
         if (mixed) zero(c, xl);
         double rmax;   // true residual at the last reliable update

@@ -176,21 +176,18 @@ __global__ void __launch_bounds__(256) k_convert(const void* in, const float* in
     }
 }
 
-// xhi += xlo ; xlo = 0
-template <int PX>
-__global__ void __launch_bounds__(256) k_accum_hi(void* xhi, void* xlo, float* xlon, size_t n5,
-                                                  size_t N) {
-    using AX = typename PT<PX>::A;
+// xhi += xlo ; xlo = 0  (FP64 and FP32 half fields; the dense solve's reliable update)
+__global__ void __launch_bounds__(256) k_accum_hi(void* xhi, void* xlo, size_t n5, size_t N) {
     for (size_t n = blockIdx.x * (size_t)blockDim.x + threadIdx.x; n < n5;
          n += (size_t)gridDim.x * blockDim.x) {
         double h[24];
-        AX l[24];
+        float l[24];
         ld_spinor<P64>(xhi, nullptr, N, n, h);
-        ld_spinor<PX>(xlo, xlon, N, n, l);
+        ld_spinor<P32>(xlo, nullptr, N, n, l);
 #pragma unroll
         for (int k = 0; k < 24; ++k) { h[k] += (double)l[k]; l[k] = 0; }
         st_spinor<P64>(xhi, nullptr, N, n, h);
-        st_spinor<PX>(xlo, xlon, N, n, l);
+        st_spinor<P32>(xlo, nullptr, N, n, l);
     }
 }
 
@@ -385,13 +382,8 @@ hipError_t launch_convert(int pi, int po, const void* in, const float* inn, void
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_accum_hi(int px, void* xhi, void* xlo, float* xlon, size_t n5, size_t N, int nblk,
-                           hipStream_t st) {
-    switch (px) {
-    case P64: hipLaunchKernelGGL((k_accum_hi<P64>), dim3(nblk), dim3(256), 0, st, xhi, xlo, xlon, n5, N); break;
-    case P32: hipLaunchKernelGGL((k_accum_hi<P32>), dim3(nblk), dim3(256), 0, st, xhi, xlo, xlon, n5, N); break;
-    default: return hipErrorInvalidValue;
-    }
+hipError_t launch_accum_hi(void* xhi, void* xlo, size_t n5, size_t N, int nblk, hipStream_t st) {
+    hipLaunchKernelGGL(k_accum_hi, dim3(nblk), dim3(256), 0, st, xhi, xlo, n5, N);
     return hipGetLastError();
 }
 

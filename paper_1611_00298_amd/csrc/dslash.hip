@@ -1188,10 +1188,11 @@ __device__ __forceinline__ double block_sum(double x, double* red) {
     return t;
 }
 
-// NAT (FP64 hops that end dwf_apply): the diagonal term's operand is read from
+// IO = 1, NAT (FP64 hops that end dwf_apply): the diagonal term's operand is read from
 // the natural layout and the result written to it, through the epilogue's
 // tile.  At 24^3x64, Ls = 24 the hop takes 1.90 ms instead of 1.74 ms plus its
 // share of two layout passes (2.26 ms); dwf_apply 9.55 -> 5.32 ms.
+// IO = 1 + p (FP64 hops): the result is stored in precision p.
 // LAT (per-site hops of small grids): nothing hides a wavefront's latency, so
 // every operand is requested up front -- links, 8 (FP32: 5, FP64: 4)
 // neighbours, aux fields -- at a register budget of two wavefronts per SIMD
@@ -1203,10 +1204,11 @@ __device__ __forceinline__ const T* behind(const T* p, size_t bytes) {
     return reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + bytes);
 }
 
-template <int P, bool DAG, bool HOP, int MF, bool DENSE = false, bool BLK = false, bool NAT = false, bool LAT = false>
+template <int P, bool DAG, bool HOP, int MF, bool DENSE = false, bool BLK = false, int IO = 0, bool LAT = false>
 __global__ void __launch_bounds__(256, LAT ? (P == P64 ? 1 : 2) : (MF == 3 && P == P16 && !DENSE) ? 5 : 3) k_hop(const HopArgs args) {
     using A = typename PT<P>::A;
     // (the FP64 throughput forms would spill more: their reductions stay launches of their own)
+    constexpr bool NAT = IO == 1;
     constexpr bool RED = (P != P64 || LAT) && DAG && HOP && !DENSE && !NAT;
     // column-sweep load batch: what each variant's register budget allows
     constexpr int COLB = LAT ? 8 : P == P64 ? 1 : (P == P16 && MF) ? 4 : 8;
@@ -1414,7 +1416,16 @@ __global__ void __launch_bounds__(256, LAT ? (P == P64 ? 1 : 2) : (MF == 3 && P 
         nat_rows_store(a.out_nat, rowoff, a.NS * Ls, lds, a.zero_pair != 0);
         return;
     }
-    if (active) st_spinor<P, true>(a.out, a.out_nrm, a.N, n, v);
+    if constexpr (IO > 1) {
+        if (active) {
+            typename PT<IO - 1>::A o[24];
+#pragma unroll
+            for (int k = 0; k < 24; ++k) o[k] = (typename PT<IO - 1>::A)v[k];
+            st_spinor<IO - 1, true>(a.out, a.out_nrm, a.N, n, o);
+        }
+    } else {
+        if (active) st_spinor<P, true>(a.out, a.out_nrm, a.N, n, v);
+    }
     if (a.partial) {
         double x = 0;
         if (active) {
@@ -1498,6 +1509,43 @@ __global__ void __launch_bounds__(256) k_pupdate(const void* z, const float* z_n
     A t[24];
     row_bidiag(lds, tid, s, Ls, v, t, (A)b5, (A)c5, 0, (A)mp_, (A)mm_);
     if (active) st_spinor<P>(pt, pt_nrm, N, n, t);
+}
+
+// ---------------------------------------------------------------------------
+// Reliable update of the solution: x += Dtilde^-1 xl, xl = 0, xt = Dtilde x, in
+// one pass (xl holds Dtilde times the update).  Bound by memory: 24^3x16, Ls = 24
+// in 357 us (2.0 GB), three passes for the same 587 us.
+// ---------------------------------------------------------------------------
+template <int PX>
+__global__ void __launch_bounds__(256) k_fold(void* x, void* xl, void* xt, int Vh, int Ls, int NS, size_t N, double b5,
+                                              double c5, double mp, double mm) {
+    using A = typename PT<PX>::A;
+    extern __shared__ unsigned char smem_raw[];
+    const int tid = threadIdx.x, sl = tid / Ls, s = tid - sl * Ls;
+    const int site = xcd_block(gridDim.x) * NS + sl;
+    const bool active = site < Vh;
+    const size_t n = active ? (size_t)site * Ls + s : 0;
+    RawSpinor<P64> rx;
+    rx.load(x, nullptr, N, n);
+    A v[24];
+    ld_spinor<PX>(xl, nullptr, N, n, v);
+    column_phase<8>(reinterpret_cast<A*>(smem_raw), tid, sl, s, Ls, v, Op5{0, 0, 0.0, 0.0}, A(1), Op5{2, 0, b5, c5},
+                    (A)mp, (A)mm);
+    double h[24];
+    rx.get(h);
+#pragma unroll
+    for (int k = 0; k < 24; ++k) h[k] += (double)v[k];
+    double* T = reinterpret_cast<double*>(smem_raw);
+    put_row(T, tid, h);
+    __syncthreads();
+    if (!active) return;
+    st_spinor<P64, true>(x, nullptr, N, n, h);
+    double y[24];
+    row_bidiag(T, tid, s, Ls, h, y, b5, c5, 0, mp, mm);
+    st_spinor<P64, true>(xt, nullptr, N, n, y);
+#pragma unroll
+    for (int k = 0; k < 24; ++k) v[k] = 0;
+    st_spinor<PX, true>(xl, nullptr, N, n, v);
 }
 
 // ---------------------------------------------------------------------------
@@ -1603,6 +1651,19 @@ static NatArgs nat_args(const int L[4], int Ls, size_t N, int par, void* e, floa
     return a;
 }
 
+hipError_t launch_fold(int px, void* x, void* xl, void* xt, int Vh, int Ls, int NS, size_t N, double b5, double c5,
+                       double mp, double mm, int nblk, hipStream_t st) {
+    const int NT = NS * Ls;
+    const size_t shm = (size_t)STR * NT * sizeof(double);
+    if (px == P32)
+        hipLaunchKernelGGL((k_fold<P32>), dim3(nblk), dim3(NT), shm, st, x, xl, xt, Vh, Ls, NS, N, b5, c5, mp, mm);
+    else if (px == P64)
+        hipLaunchKernelGGL((k_fold<P64>), dim3(nblk), dim3(NT), shm, st, x, xl, xt, Vh, Ls, NS, N, b5, c5, mp, mm);
+    else
+        return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
 hipError_t launch_nat_to_dev(int prec, const void* nat, void* e, float* en, void* o, float* on, int par, const Op5& B,
                              double mp, double mm, const int L[4], int Ls, size_t N, hipStream_t st) {
     int NT;
@@ -1657,7 +1718,7 @@ static hipError_t launch_hop_t(const HopArgs& a, int nblk, hipStream_t st) {
         if (a.frag) {
             const size_t shm = std::max(tile, stage_bytes(LinkLds<P, 1>::LB, a.NS) + (a.blk ? share_bytes(P, true, NT) : 0));
             if (a.lat) {
-                hipLaunchKernelGGL((k_hop<P, DAG, HOP, 3, false, false, false, true>), dim3(nblk), dim3(NT), shm, st, a);
+                hipLaunchKernelGGL((k_hop<P, DAG, HOP, 3, false, false, 0, true>), dim3(nblk), dim3(NT), shm, st, a);
                 return hipGetLastError();
             }
             if (a.blk) {   // the block path keeps its own loads in flight
@@ -1679,9 +1740,30 @@ static hipError_t launch_hop_t(const HopArgs& a, int nblk, hipStream_t st) {
             const size_t links = a.blk ? (size_t)(2 * a.NS + 1) * LinkLds<P, 0>::LB + share_bytes(P, false, NT)
                                        : stage_bytes(LinkLds<P, 0>::LB, a.NS);
             const size_t shm = std::max((size_t)STR * NT * sizeof(A), links);
-            if (a.lat) hipLaunchKernelGGL((k_hop<P, DAG, HOP, 0, false, false, true, true>), dim3(nblk), dim3(NT), shm, st, a);
-            else if (a.blk) hipLaunchKernelGGL((k_hop<P, DAG, HOP, 0, false, true, true>), dim3(nblk), dim3(NT), shm, st, a);
-            else hipLaunchKernelGGL((k_hop<P, DAG, HOP, 0, false, false, true>), dim3(nblk), dim3(NT), shm, st, a);
+            if (a.lat) hipLaunchKernelGGL((k_hop<P, DAG, HOP, 0, false, false, 1, true>), dim3(nblk), dim3(NT), shm, st, a);
+            else if (a.blk) hipLaunchKernelGGL((k_hop<P, DAG, HOP, 0, false, true, 1>), dim3(nblk), dim3(NT), shm, st, a);
+            else hipLaunchKernelGGL((k_hop<P, DAG, HOP, 0, false, false, 1>), dim3(nblk), dim3(NT), shm, st, a);
+            return hipGetLastError();
+        }
+    }
+    if constexpr (P == P64 && HOP && !DAG) {
+        if (a.out_prec) {   // the result in a lower precision (the reliable update's residual)
+            const size_t links = a.blk ? (size_t)(2 * a.NS + 1) * LinkLds<P, 0>::LB + share_bytes(P, false, NT)
+                                       : stage_bytes(LinkLds<P, 0>::LB, a.NS);
+            const size_t shm = std::max(tile, links);
+            switch (a.out_prec) {
+#define EOFA_CASE(PP)                                                                                              \
+    case PP:                                                                                                       \
+        if (a.blk) hipLaunchKernelGGL((k_hop<P, DAG, HOP, 0, false, true, 1 + PP>), dim3(nblk), dim3(NT), shm, st, a);       \
+        else if (a.lat) hipLaunchKernelGGL((k_hop<P, DAG, HOP, 0, false, false, 1 + PP, true>), dim3(nblk), dim3(NT), shm, st, a); \
+        else hipLaunchKernelGGL((k_hop<P, DAG, HOP, 0, false, false, 1 + PP>), dim3(nblk), dim3(NT), shm, st, a);            \
+        break;
+                EOFA_CASE(P32)
+                EOFA_CASE(P16)
+                EOFA_CASE(PB16)
+#undef EOFA_CASE
+            default: return hipErrorInvalidValue;
+            }
             return hipGetLastError();
         }
     }
@@ -1697,7 +1779,7 @@ static hipError_t launch_hop_t(const HopArgs& a, int nblk, hipStream_t st) {
     const size_t shm = HOP ? std::max(tile, stage_bytes(LinkLds<P, 0>::LB, a.NS)) : tile;
     if constexpr (HOP) {
         if (a.lat) {
-            hipLaunchKernelGGL((k_hop<P, DAG, HOP, 0, false, false, false, true>), dim3(nblk), dim3(NT), shm, st, a);
+            hipLaunchKernelGGL((k_hop<P, DAG, HOP, 0, false, false, 0, true>), dim3(nblk), dim3(NT), shm, st, a);
             return hipGetLastError();
         }
     }

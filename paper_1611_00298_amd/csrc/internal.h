@@ -345,6 +345,7 @@ struct HopArgs {
     const int* nbr;      // neighbour cb index of the output parity, [8][Vh]
     const int* sites;    // traversal: slot lb*NS + sl -> output site, >= Vh for padding (nullable)
     const void* frag;    // compact FP16 links for the matrix-core path, [8][Vh][9] (re, im) halves (nullable)
+    int out_prec;        // FP64 hops: store the result in this precision (0: FP64)
     int depth;           // directions of operands kept in flight (matrix-core path)
     int par;             // parity of the output sites
     int blk;             // the site table lists whole 2x2x2x2 blocks, 8 slots each (block-sharing hops)
