@@ -230,6 +230,17 @@ void* rawbuf(eofa_ctx* c, const std::string& name, size_t bytes) {
     return c->raw[name] = p;
 }
 
+bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+    return (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
+
+// a copy of an operand whose memory a kernel's result shares
+const void* copy_aside(eofa_ctx* c, const char* name, const void* src, size_t bytes) {
+    void* p = rawbuf(c, name, bytes);
+    hipchk(hipMemcpyAsync(p, src, bytes, hipMemcpyDeviceToDevice, c->st), "hipMemcpy(operand)");
+    return p;
+}
+
 void* gauge_of(eofa_ctx* c, int prec) {
     if (!c->gauge[prec]) {
         const size_t nc = (size_t)2 * 8 * 9 * c->Vh;
@@ -2015,6 +2026,8 @@ int dwf_apply(eofa_ctx_t* c, double mp, double mm, int dagger, int eo, eofa_prec
         if (in == out) fail(EOFA_EINVAL, "in and out may not alias");
         const int P = prec;
         if (P == P64) {
+            const size_t nb5 = (size_t)c->Ls * c->V * 192;
+            if (overlap(in, nb5, out, nb5)) in = copy_aside(c, "ap_nat", in, nb5);
             // FP64: the hop's input goes to the device layout (already Dtilde in
             // where the hop needs that); the hop that ends the operator reads
             // the diagonal term's operand from `in` and writes `out` itself
@@ -2136,9 +2149,9 @@ int eofa_force(eofa_ctx_t* c, double m1, double m2, const void* phi, const void*
         double k;
         omega_k(c, m1, m2, &k);
         int status = EOFA_OK;
+        const size_t nb5 = (size_t)c->Ls * c->V * 192, nb4 = (size_t)4 * c->V * 144;
         if (!chiL || !chiR) {
             if (!phi) fail(EOFA_EINVAL, "phi is needed when chi is not given");
-            const size_t nb5 = (size_t)c->Ls * c->V * 12 * 16;
             void* cl = rawbuf(c, "force_chiL", nb5);
             void* cr = rawbuf(c, "force_chiR", nb5);
             status = solve_impl(c, m1, m2, phi, nullptr, nullptr, cl, cr, nullptr, nullptr, sp, stats);
@@ -2146,6 +2159,11 @@ int eofa_force(eofa_ctx_t* c, double m1, double m2, const void* phi, const void*
             chiL = cl;
             chiR = cr;
         }
+        // F and G may share memory with chi, which the kernel reads throughout
+        if (overlap(chiL, nb5, F, nb4) || (G && overlap(chiL, nb5, G, nb4)))
+            chiL = copy_aside(c, "force_chiL", chiL, nb5);
+        if (overlap(chiR, nb5, F, nb4) || (G && overlap(chiR, nb5, G, nb4)))
+            chiR = copy_aside(c, "force_chiR", chiR, nb5);
         const int ev = timing_begin(c);
         hipchk(launch_force(c->U_nat, chiL, chiR, k, F, G, c->L, c->Ls, c->aperiodic, c->st), "force");
         // algorithmic bytes: chi_L and chi_R once, U, F (and G)
