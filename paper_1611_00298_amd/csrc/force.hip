@@ -92,7 +92,10 @@ struct ForceTile {
     int n[4];    // tiles along each direction
 };
 
-// acc += sum_j h_j (x) g_j^dag, h_j of the spinor at p and g_j of the one at q
+// acc += sum_j h_j (x) g_j^dag, h_j of the spinor at p and g_j of the one at q.
+// The slice's four products are summed before they join the accumulator: 2 Ls
+// roundings at the size of the whole sum would be 8 Ls, and an error 2.2 times
+// as large at Ls = 16, with each product added to the accumulator by itself.
 template <int MU>
 __device__ __forceinline__ void force_pair(const d2v* __restrict__ p, const d2v* __restrict__ q,
                                            cplx (&acc)[9]) {
@@ -112,16 +115,14 @@ __device__ __forceinline__ void force_pair(const d2v* __restrict__ p, const d2v*
         gg[1][cc] = {b1.x - q1.r, b1.y - q1.i};
     }
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int x = 0; x < 3; ++x)
 #pragma unroll
-        for (int x = 0; x < 3; ++x)
-#pragma unroll
-            for (int y = 0; y < 3; ++y) {
-                const cplx u = h[j][x], v = gg[j][y];
-                cplx& o = acc[3 * x + y];
-                o.r = fmadd(u.r, v.r, fmadd(u.i, v.i, o.r));
-                o.i = fmadd(u.i, v.r, fmadd(-u.r, v.i, o.i));
-            }
+        for (int y = 0; y < 3; ++y) {
+            const cplx u0 = h[0][x], v0 = gg[0][y], u1 = h[1][x], v1 = gg[1][y];
+            cplx& o = acc[3 * x + y];
+            o.r += fmadd(u1.r, v1.r, fmadd(u1.i, v1.i, fmadd(u0.r, v0.r, u0.i * v0.i)));
+            o.i += fmadd(u1.i, v1.r, fmadd(-u1.r, v1.i, fmadd(u0.i, v0.r, -u0.r * v0.i)));
+        }
 }
 
 __global__ void __launch_bounds__(256, 2) k_force(const double2* __restrict__ chiL, const double2* __restrict__ chiR,
@@ -199,7 +200,7 @@ __global__ void __launch_bounds__(256, 2) k_force(const double2* __restrict__ ch
 #pragma unroll
         for (int u = 0; u < FT_LOADS; ++u) vb[u] = b[src[u]];
     };
-    cplx acc[9];
+    cplx acc[9], accL[9];   // this system's sum, and chi_L's once it is complete
 #pragma unroll
     for (int q = 0; q < 9; ++q) acc[q] = {0.0, 0.0};
     fetch(0);
@@ -226,15 +227,20 @@ __global__ void __launch_bounds__(256, 2) k_force(const double2* __restrict__ ch
             default: force_pair<3>(p, w, acc); break;
             }
         }
-        if (it == half - 1) {   // chi_R enters with the opposite sign: acc = -B[chi_L] + B[chi_R] from here
+        if (it == half - 1) {
 #pragma unroll
-            for (int e = 0; e < 9; ++e) acc[e] = {-acc[e].r, -acc[e].i};
+            for (int e = 0; e < 9; ++e) {
+                accL[e] = acc[e];
+                acc[e] = {0.0, 0.0};
+            }
         }
     }
+#pragma unroll
+    for (int e = 0; e < 9; ++e) acc[e] = {accL[e].r - acc[e].r, accL[e].i - acc[e].i};
     if (active) {
         const double sigma = (mu == 3 && g.aperiodic && o[3] + own[3] == g.L[3] - 1) ? -1.0 : 1.0;
         const size_t l = ((size_t)mu * g.V + nat[lane]) * 9;
-        force_from_B(acc, U + l, -sigma, k, F + l, G ? G + l : nullptr);
+        force_from_B(acc, U + l, sigma, k, F + l, G ? G + l : nullptr);
     }
 }
 
