@@ -77,7 +77,8 @@ int action_blocks(int V);
 hipError_t launch_eofa_action(const void* phi, const void* chiL, const void* chiR, const double* om,
                               double k, void* Mphi, double* partial, int V, int Ls, hipStream_t st);
 hipError_t launch_force(const void* U, const void* chiL, const void* chiR, double k, void* F, void* G,
-                        const int L[4], int Ls, int aperiodic, hipStream_t st);
+                        const int L[4], int Ls, int aperiodic, void* part, hipStream_t st);
+size_t force_workspace(const int L[4], int Ls);
 int md_blocks(int nlink);
 hipError_t md_scratch_address(double** out);
 hipError_t launch_md_update(void* U, void* P, const void* F, double dt_p, double dt_u, int nlink,
@@ -2164,8 +2165,10 @@ int eofa_force(eofa_ctx_t* c, double m1, double m2, const void* phi, const void*
             chiL = copy_aside(c, "force_chiL", chiL, nb5);
         if (overlap(chiR, nb5, F, nb4) || (G && overlap(chiR, nb5, G, nb4)))
             chiR = copy_aside(c, "force_chiR", chiR, nb5);
+        const size_t nw = force_workspace(c->L, c->Ls);
+        void* part = nw ? rawbuf(c, "force_part", nw) : nullptr;
         const int ev = timing_begin(c);
-        hipchk(launch_force(c->U_nat, chiL, chiR, k, F, G, c->L, c->Ls, c->aperiodic, c->st), "force");
+        hipchk(launch_force(c->U_nat, chiL, chiR, k, F, G, c->L, c->Ls, c->aperiodic, part, c->st), "force");
         // algorithmic bytes: chi_L and chi_R once, U, F (and G)
         timing_end(c, ev, C_FORCE, 2.0 * c->V * c->Ls * 192.0 + 4.0 * c->V * 144.0 * (G ? 3.0 : 2.0));
         hipchk(hipStreamSynchronize(c->st), "hipStreamSynchronize");

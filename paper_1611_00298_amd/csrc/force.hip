@@ -90,7 +90,23 @@ constexpr int FT_LOADS = (FT_CHUNKS + 255) / 256;
 struct ForceTile {
     int lg[4];   // log2 of the tile extents (1 or 2)
     int n[4];    // tiles along each direction
+    int tiles;
+    int split;   // > 0: ranges of slice pairs per system, each a workgroup's
 };
+
+// origin of tile r, and a lane's site in it (own); false: beyond the lattice
+__device__ __forceinline__ bool tile_site(const ForceTile& ft, const Geo& g, int r, int lane, int (&o)[4], int (&own)[4]) {
+    bool active = true;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        o[d] = (r % ft.n[d]) << ft.lg[d];
+        r /= ft.n[d];
+        own[d] = lane & ((1 << ft.lg[d]) - 1);
+        lane >>= ft.lg[d];
+        active = active && o[d] + own[d] < g.L[d];
+    }
+    return active;
+}
 
 // acc += sum_j h_j (x) g_j^dag, h_j of the spinor at p and g_j of the one at q.
 // The slice's four products are summed before they join the accumulator: 2 Ls
@@ -125,21 +141,19 @@ __device__ __forceinline__ void force_pair(const d2v* __restrict__ p, const d2v*
         }
 }
 
+// Small lattices have few tiles: with SPLIT, a workgroup takes one system and
+// one of ft.split ranges of its slice pairs and leaves its sums in part,
+// [2 split][tile][9][256]; k_force_finish adds them up.
+template <bool SPLIT>
 __global__ void __launch_bounds__(256, 2) k_force(const double2* __restrict__ chiL, const double2* __restrict__ chiR,
                                                   const double2* __restrict__ U, double k, double2* __restrict__ F,
-                                                  double2* __restrict__ G, Geo g, ForceTile ft) {
+                                                  double2* __restrict__ G, Geo g, ForceTile ft, double2* __restrict__ part) {
     __shared__ d2v tile[2][12 * FT_STR];
     __shared__ int nat[FT_SLOTS];   // natural site index of each slot
     const int tid = threadIdx.x, mu = tid >> 6, lane = tid & 63;
-    int o[4];   // tile origin
-    {
-        int r = xcd_block(gridDim.x);
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            o[d] = (r % ft.n[d]) << ft.lg[d];
-            r /= ft.n[d];
-        }
-    }
+    const int blk = xcd_block(gridDim.x), rng = SPLIT ? blk / ft.tiles : 0;
+    int o[4], own[4];   // tile origin, this lane's site
+    const bool active = tile_site(ft, g, blk - rng * ft.tiles, lane, o, own);
     // first slot of each face
     int face[4];
     face[0] = FT_SITES;
@@ -160,21 +174,14 @@ __global__ void __launch_bounds__(256, 2) k_force(const double2* __restrict__ ch
         }
         nat[tid] = i;
     }
-    // this lane's site, and the slot of its neighbour along mu
-    int own[4], r = lane, nb = 0, sh = 0;
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        own[d] = r & ((1 << ft.lg[d]) - 1);
-        r >>= ft.lg[d];
-    }
-    bool inside = true, active = true;
-    int step = 1;
+    // the slot of this lane's neighbour along mu
+    int nb = 0, sh = 0, step = 1;
+    bool inside = true;
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
         if (d == mu) inside = own[d] + 1 < (1 << ft.lg[d]);
         else { nb |= own[d] << sh; sh += ft.lg[d]; }
         if (d < mu) step <<= ft.lg[d];
-        active = active && o[d] + own[d] < g.L[d];
     }
     nb = inside ? lane + step : nb + (mu == 0 ? face[0] : mu == 1 ? face[1] : mu == 2 ? face[2] : face[3]);
     __syncthreads();
@@ -203,9 +210,15 @@ __global__ void __launch_bounds__(256, 2) k_force(const double2* __restrict__ ch
     cplx acc[9], accL[9];   // this system's sum, and chi_L's once it is complete
 #pragma unroll
     for (int q = 0; q < 9; ++q) acc[q] = {0.0, 0.0};
-    fetch(0);
+    int it0 = 0, it1 = 2 * half;
+    if constexpr (SPLIT) {
+        const int sys = rng >= ft.split, j = rng - sys * ft.split;
+        it0 = sys * half + half * j / ft.split;
+        it1 = sys * half + half * (j + 1) / ft.split;
+    }
+    fetch(it0);
 #pragma unroll 1
-    for (int it = 0; it < 2 * half; ++it) {
+    for (int it = it0; it < it1; ++it) {
         __syncthreads();   // the previous step's slices are read
 #pragma unroll
         for (int u = 0; u < FT_LOADS; ++u) {
@@ -213,7 +226,7 @@ __global__ void __launch_bounds__(256, 2) k_force(const double2* __restrict__ ch
             tile[1][dst[u]] = vb[u];
         }
         __syncthreads();
-        if (it + 1 < 2 * half) fetch(it + 1);   // in flight while this step computes
+        if (it + 1 < it1) fetch(it + 1);   // in flight while this step computes
         const int q = it < half ? it : it - half;
         const int n = 2 * q + 1 == Ls ? 1 : 2;   // the middle slice of an odd Ls pairs with itself
 #pragma unroll 1
@@ -227,13 +240,19 @@ __global__ void __launch_bounds__(256, 2) k_force(const double2* __restrict__ ch
             default: force_pair<3>(p, w, acc); break;
             }
         }
-        if (it == half - 1) {
+        if (!SPLIT && it == half - 1) {
 #pragma unroll
             for (int e = 0; e < 9; ++e) {
                 accL[e] = acc[e];
                 acc[e] = {0.0, 0.0};
             }
         }
+    }
+    if constexpr (SPLIT) {
+        double2* dst2 = part + (size_t)blk * 9 * 256 + tid;
+#pragma unroll
+        for (int e = 0; e < 9; ++e) dst2[e * 256] = make_double2(acc[e].r, acc[e].i);
+        return;
     }
 #pragma unroll
     for (int e = 0; e < 9; ++e) acc[e] = {accL[e].r - acc[e].r, accL[e].i - acc[e].i};
@@ -242,6 +261,41 @@ __global__ void __launch_bounds__(256, 2) k_force(const double2* __restrict__ ch
         const size_t l = ((size_t)mu * g.V + nat[lane]) * 9;
         force_from_B(acc, U + l, sigma, k, F + l, G ? G + l : nullptr);
     }
+}
+
+// F and G from the sums of k_force<true>, one tile per workgroup, in the order of the ranges
+__global__ void __launch_bounds__(256) k_force_finish(const double2* __restrict__ part, const double2* __restrict__ U,
+                                                      double k, double2* __restrict__ F, double2* __restrict__ G, Geo g,
+                                                      ForceTile ft) {
+    const int tid = threadIdx.x, mu = tid >> 6;
+    int o[4], own[4];
+    if (!tile_site(ft, g, blockIdx.x, tid & 63, o, own)) return;
+    cplx B[2][9];
+#pragma unroll
+    for (int sys = 0; sys < 2; ++sys) {
+#pragma unroll
+        for (int e = 0; e < 9; ++e) B[sys][e] = {0.0, 0.0};
+        for (int j = 0; j < ft.split; ++j) {
+            const double2* p = part + ((size_t)(sys * ft.split + j) * ft.tiles + blockIdx.x) * 9 * 256 + tid;
+#pragma unroll
+            for (int e = 0; e < 9; ++e) {
+                const double2 v = p[e * 256];
+                B[sys][e].r += v.x;
+                B[sys][e].i += v.y;
+            }
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 9; ++e) B[0][e] = {B[0][e].r - B[1][e].r, B[0][e].i - B[1][e].i};
+    int i = 0, stride = 1;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        i += (o[d] + own[d]) * stride;
+        stride *= g.L[d];
+    }
+    const double sigma = (mu == 3 && g.aperiodic && o[3] + own[3] == g.L[3] - 1) ? -1.0 : 1.0;
+    const size_t l = ((size_t)mu * g.V + i) * 9;
+    force_from_B(B[0], U + l, sigma, k, F + l, G ? G + l : nullptr);
 }
 
 // ---------------------------------------------------------------------------
@@ -325,29 +379,57 @@ __global__ void __launch_bounds__(256) k_md_update(double2* __restrict__ U, doub
 // share those faces in its L2, while the z and t faces, halved by the longer
 // extents, come from beyond it (24^3x64, Ls = 24: 3.10 ms against 3.37 ms
 // with the long extents along x and y).
+//
+// The split: one workgroup per tile walks its slice pairs in a row, 1.9 us each
+// on an idle GPU, so up to 128 tiles (half of the 256 CUs) the pairs of a system
+// are shared out to sqrt(Ls) workgroups (walks and the sum over them grow
+// alike), at most two workgroups per CU.  A call at 4^4: Ls = 8 35.6 -> 29.5 us,
+// Ls = 24 65.9 -> 33.9, Ls = 64 145 -> 41.7; 8^4, Ls = 24 69.4 -> 41.3 us;
+// 8^3x16, Ls = 8 38.6 -> 37.6 us.  Beyond the line the second launch costs what
+// the shorter walks save: 8^3x32 (256 tiles), Ls = 8 40.9 against 44.1 us, and
+// below Ls = 8 too: 8^4, Ls = 4 29.0 against 32.2 us.
+static ForceTile force_tiling(const int L[4], int Ls) {
+    ForceTile ft{};
+    for (int a = 0; a < 3; ++a)
+        for (int b = a + 1; b < 4; ++b) {
+            ForceTile c{};
+            c.tiles = 1;
+            for (int d = 0; d < 4; ++d) {
+                c.lg[d] = d == a || d == b ? 2 : 1;
+                c.n[d] = (L[d] + (1 << c.lg[d]) - 1) >> c.lg[d];
+                c.tiles *= c.n[d];
+            }
+            if (ft.tiles == 0 || c.tiles <= ft.tiles) ft = c;
+        }
+    if (ft.tiles <= 128 && Ls >= 8) ft.split = std::min((int)std::sqrt((double)Ls), 256 / ft.tiles);
+    return ft;
+}
+
+size_t force_workspace(const int L[4], int Ls) {
+    const ForceTile ft = force_tiling(L, Ls);
+    return (size_t)2 * ft.split * ft.tiles * 9 * 256 * sizeof(double2);
+}
+
 hipError_t launch_force(const void* U, const void* chiL, const void* chiR, double k, void* F, void* G,
-                        const int L[4], int Ls, int aperiodic, hipStream_t st) {
+                        const int L[4], int Ls, int aperiodic, void* part, hipStream_t st) {
     Geo g;
     for (int mu = 0; mu < 4; ++mu) g.L[mu] = L[mu];
     g.V = L[0] * L[1] * L[2] * L[3];
     g.Vh = g.V / 2;
     g.Ls = Ls;
     g.aperiodic = aperiodic;
-    ForceTile ft{};
-    long best = 0;
-    for (int a = 0; a < 3; ++a)
-        for (int b = a + 1; b < 4; ++b) {
-            ForceTile c;
-            long tiles = 1;
-            for (int d = 0; d < 4; ++d) {
-                c.lg[d] = d == a || d == b ? 2 : 1;
-                c.n[d] = (L[d] + (1 << c.lg[d]) - 1) >> c.lg[d];
-                tiles *= c.n[d];
-            }
-            if (best == 0 || tiles <= best) { best = tiles; ft = c; }
-        }
-    hipLaunchKernelGGL(k_force, dim3((unsigned)best), dim3(256), 0, st, (const double2*)chiL, (const double2*)chiR,
-                       (const double2*)U, k, (double2*)F, (double2*)G, g, ft);
+    const ForceTile ft = force_tiling(L, Ls);
+    const unsigned n = (unsigned)ft.tiles;
+    if (ft.split == 0) {
+        hipLaunchKernelGGL((k_force<false>), dim3(n), dim3(256), 0, st, (const double2*)chiL, (const double2*)chiR,
+                           (const double2*)U, k, (double2*)F, (double2*)G, g, ft, (double2*)nullptr);
+        return hipGetLastError();
+    }
+    if (!part) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_force<true>), dim3(n * 2 * ft.split), dim3(256), 0, st, (const double2*)chiL,
+                       (const double2*)chiR, (const double2*)U, k, (double2*)F, (double2*)G, g, ft, (double2*)part);
+    hipLaunchKernelGGL(k_force_finish, dim3(n), dim3(256), 0, st, (const double2*)part, (const double2*)U, k,
+                       (double2*)F, (double2*)G, g, ft);
     return hipGetLastError();
 }
 
