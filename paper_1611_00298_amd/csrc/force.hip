@@ -11,6 +11,7 @@
 // and g = chi_up - A_mu chi_lo at (x+mu, Ls-1-s) (the minus sign is gamma_5).
 // FP64 throughout; one work-item per link, chi in the natural layout.
 #include "internal.h"
+#include <type_traits>
 
 namespace eofa {
 
@@ -229,16 +230,15 @@ __global__ void __launch_bounds__(256, 2) k_force(const double2* __restrict__ ch
         if (it + 1 < it1) fetch(it + 1);   // in flight while this step computes
         const int q = it < half ? it : it - half;
         const int n = 2 * q + 1 == Ls ? 1 : 2;   // the middle slice of an odd Ls pairs with itself
-#pragma unroll 1
-        for (int t = 0; t < n; ++t) {
-            const d2v* p = tile[t] + lane;
-            const d2v* w = tile[1 - t] + nb;
-            switch (mu) {
-            case 0: force_pair<0>(p, w, acc); break;
-            case 1: force_pair<1>(p, w, acc); break;
-            case 2: force_pair<2>(p, w, acc); break;
-            default: force_pair<3>(p, w, acc); break;
-            }
+        auto pair = [&](auto m) __attribute__((always_inline)) {
+            force_pair<decltype(m)::value>(tile[0] + lane, tile[1] + nb, acc);
+            if (n == 2) force_pair<decltype(m)::value>(tile[1] + lane, tile[0] + nb, acc);
+        };
+        switch (mu) {   // once per pair: 8^3x32, Ls = 64 169 -> 162 us against a switch per slice
+        case 0: pair(std::integral_constant<int, 0>()); break;
+        case 1: pair(std::integral_constant<int, 1>()); break;
+        case 2: pair(std::integral_constant<int, 2>()); break;
+        default: pair(std::integral_constant<int, 3>()); break;
         }
         if (!SPLIT && it == half - 1) {
 #pragma unroll
