@@ -164,7 +164,8 @@ struct eofa_ctx {
     double M5 = 0, alpha = 0, b5 = 0, c5 = 0, beta0 = 0, beta1 = 0;
     size_t n5 = 0, N = 0;
     int NS = 0, nblk_hop = 0, nblk_blas = 0;
-    bool small_grid = false;   // the hop's grid leaves the GPU mostly idle: the latency form
+    bool small_grid = false;   // the hop's grid leaves the GPU mostly idle: workgroups of one wavefront
+    bool lat[4] = {false, false, false, false};   // the hop's latency form, per precision (on small grids)
     int* nbr = nullptr;
     int* sites[4] = {nullptr, nullptr, nullptr, nullptr};   // hop traversal (site per slot) per precision
     int blk[4] = {0, 0, 0, 0};   // the table lists whole 2x2x2x2 blocks (FP32 and matrix-core paths)
@@ -407,7 +408,7 @@ void run_hop(eofa_ctx* c, const HopCall& h) {
     a.Ls = c->Ls;
     a.NS = c->NS;
     a.N = c->N;
-    a.lat = h.hop && !h.dmat && !a.blk && c->small_grid;
+    a.lat = h.hop && !h.dmat && !a.blk && c->small_grid && (h.in_p1 || c->lat[h.prec]);
     if (a.lat) a.sites = nullptr;   // small fields: no order to gain, one dependent load less
     a.mp = h.mp;
     a.mm = h.mm;
@@ -682,7 +683,7 @@ SolveResult cgnr_schur(eofa_ctx* c, double mp, double mm, const Half& bhat, Half
     };
     // which sums ride in other launches: |w|^2 (FP64: |r|^2) in K3, |z|^2
     // (FP64: |w|^2 too) in the update that needs it
-    const bool in_k3 = prec != P64 || c->small_grid, in_p = nb <= PUPD_PARTIALS;
+    const bool in_k3 = prec != P64 || c->lat[P64], in_p = nb <= PUPD_PARTIALS;
     int cur = S_ZZ0, nxt = S_ZZ1;
     // z = Mhat^dag r ; p_0 = z ; pt = Dtilde p_0 (mixed: the ring holds Dtilde p)
     schur_k3(c, prec, r, tmp, mp, mm);
@@ -1910,7 +1911,8 @@ int eofa_ctx_create(eofa_ctx_t** out, const eofa_geom_t* g, const void* U, void*
             c->N = (c->n5 + 255) / 256 * 256;
             // workgroup: NS whole 4D sites x Ls; prefer a multiple of 64 work-items.
             // NS <= 24 keeps the LDS-staged links of the workgroup (FP64:
-            // 24 sites x 8 directions x 144 B) within 28 KB.
+            // 24 sites x 8 directions x 144 B) within 28 KB (small grids, below: up to
+            // 64 sites at Ls = 1, 76 KB).
             int ns = std::min(256 / c->Ls, 24);
             if (ns < 1) ns = 1;
             int best = ns;
@@ -1933,7 +1935,25 @@ int eofa_ctx_create(eofa_ctx_t** out, const eofa_geom_t* g, const void* U, void*
             const int ns1 = std::max(1, 64 / c->Ls);
             const long waves = (long)((c->Vh + ns1 - 1) / ns1) * ((ns1 * c->Ls + 63) / 64);
             c->small_grid = blocks_env == 1 && waves <= (ns1 * c->Ls >= 52 ? 2048 : 1024);
-            if (c->small_grid) c->NS = ns1;
+            if (c->small_grid) {
+                c->NS = ns1;
+                for (bool& l : c->lat) l = true;
+                // The FP64 form runs one wavefront per SIMD: a second round of the
+                // GPU costs as much as a full one.  80 iterations, latency form
+                // against the throughput form at the same workgroups: Ls = 8, 1024
+                // wavefronts 6.9 / 7.9 ms, 1280 10.2 / 8.9, 1536 11.4 / 9.9; Ls = 10,
+                // 1366 10.6 / 9.9; Ls = 12, 1229 9.7 / 8.8.  With a second round
+                // nearly full it wins only where whole sites of at least 16 slices
+                // fill the wavefront: 2048 wavefronts, Ls = 16 12.0 / 13.5 ms, Ls = 32
+                // 12.2 / 13.2, Ls = 64 13.5 / 14.0, but Ls = 8 13.1 / 12.3 and Ls = 12
+                // 11.8 / 11.7 ms.  Few slices leave each work-item many links to
+                // stage (72 / Ls): Ls = 4, 648 wavefronts 7.8 / 7.9 ms, 1024 9.4 / 8.8,
+                // 1296 14.7 / 10.5; Ls = 2, 64 6.8 / 6.9, 324 9.3 / 8.6; Ls = 1, 162 12.4 / 10.5.
+                const bool full2 = waves >= 1792 && c->Ls >= 16 && 64 % c->Ls == 0;
+                const long line = c->Ls > 4 ? 1024 : c->Ls > 2 ? 768 : c->Ls > 1 ? 64 : 0;
+                c->lat[P64] = waves <= line || full2;
+                if (c->Ls == 1) c->lat[P16] = c->lat[PB16] = false;   // 8^3x32 (128): FP16 8.6 / 8.3 ms
+            }
             if (const char* e = getenv("EOFA_NS")) {   // tuning override: sites per workgroup
                 const int q = atoi(e);
                 if (q >= 1 && q <= 24 && q * c->Ls <= 256) c->NS = q;
