@@ -1828,6 +1828,7 @@ std::vector<int> block_neighbours(const eofa_ctx* c, const std::vector<int>& ord
 //   EOFA_TILE="p<py>,<pz>,<pt>,ty,tz,tt,sweep" py x pz x pt regions (e.g. "p1,2,4,6,12,1,t")
 //   EOFA_TILE="q<px>,<py>,<pz>,<pt>,tx,ty,tz,tt,sweep"  also split and tile x (tx <= 0: whole rows)
 //   EOFA_TILE="none"                          natural order
+// With EOFA_TILE set, small grids too take the forms that follow the table.
 Tiling default_tiling(const eofa_ctx* c, int prec, bool blocks) {
     Tiling T{{1, 1, 1, 1}, 3, {prec == P16 ? 4 : 8, 1, 1}, 0};
     if (blocks) {
@@ -1934,7 +1935,8 @@ int eofa_ctx_create(eofa_ctx_t** out, const eofa_geom_t* g, const void* U, void*
             // latency: 12^3x24, Ls = 12 (4148) 472 against 495 ms.
             const int ns1 = std::max(1, 64 / c->Ls);
             const long waves = (long)((c->Vh + ns1 - 1) / ns1) * ((ns1 * c->Ls + 63) / 64);
-            c->small_grid = blocks_env == 1 && waves <= (ns1 * c->Ls >= 52 ? 2048 : 1024);
+            // (Not where a tuning override asks for a form or an order: it has neither.)
+            c->small_grid = blocks_env == 1 && !getenv("EOFA_TILE") && waves <= (ns1 * c->Ls >= 52 ? 2048 : 1024);
             if (c->small_grid) {
                 c->NS = ns1;
                 for (bool& l : c->lat) l = true;
