@@ -798,7 +798,10 @@ SolveResult cgnr_schur(eofa_ctx* c, double mp, double mm, const Half& bhat, Half
     // FP64: plain CGNR with the recursively updated residual r.  The host
     // reads |r|^2 of iteration k after it has queued the rest of that
     // iteration, so that the GPU does not wait for it; at convergence that
-    // rest (the next direction) is left unused.
+    // rest (the next direction, half an iteration's work) is left unused.  On
+    // grids of more than 2048 workgroups, where it costs more than the waits
+    // of some 10 us that it saves near the end (4.5 ms at 24^3x64, Ls = 24), the
+    // host looks first once |r| is within a factor 4 of the threshold.
     Half& pt = *ptp;
     while (res.iters < maxiter) {
         Half& p = *pr[k % XBATCH];
@@ -817,22 +820,24 @@ SolveResult cgnr_schur(eofa_ctx* c, double mp, double mm, const Half& bhat, Half
         }
         res.iters++;
         double* rr_k = c->ring + 4 * (k & 1);
-        const bool more = res.iters < maxiter;
-        if (!more || !in_k3) {
+        const bool more = res.iters < maxiter, ahead = more && (in_p || rr > 16.0 * thresh * thresh);
+        if (!ahead || !in_k3) {
             hipchk(launch_reduce(part_r, c->nblk_blas, RedOut{c->sc, S_RR, rr_k, S_RR, 1}, c->st), "reduce");
             hipchk(hipEventRecord(c->ring_ev[k & 1], c->st), "hipEventRecord");
         }
         if (k - pending0 + 1 == XBATCH) flush(k);
-        if (more) {
-            // z = Mhat^dag r, |z|^2 ; p_{k+1} = z + beta p_k ; pt = Dtilde p_{k+1}
-            schur_k3(c, prec, r, tmp, mp, mm, in_k3 ? c->nblk_blas : 0, S_RR, rr_k, part_r);
-            if (in_k3) hipchk(hipEventRecord(c->ring_ev[k & 1], c->st), "hipEventRecord");
+        // z = Mhat^dag r, |z|^2 ; p_{k+1} = z + beta p_k ; pt = Dtilde p_{k+1}
+        auto next_direction = [&]() {
+            const bool ride = ahead && in_k3;   // |r|^2 is summed by K3
+            schur_k3(c, prec, r, tmp, mp, mm, ride ? c->nblk_blas : 0, S_RR, rr_k, part_r);
+            if (ride) hipchk(hipEventRecord(c->ring_ev[k & 1], c->st), "hipEventRecord");
             schur_k4(c, prec, tmp, r, z, mp, mm, c->partial);
             if (!in_p) reduce(c, nb, nxt);
             Half& pn1 = *pr[(k + 1) % XBATCH];
             pupdate(c, prec, z, &p, pn1, &pt, nxt, cur, mp, mm, in_p ? nb : 0);
             c->flops += 72.0 * (double)c->n5 + 48.0 * (double)c->n5;
-        }
+        };
+        if (ahead) next_direction();
         hipchk(hipEventSynchronize(c->ring_ev[k & 1]), "hipEventSynchronize");
         rr = rr_k[0];
         check_finite(rr, "residual norm");
@@ -841,6 +846,7 @@ SolveResult cgnr_schur(eofa_ctx* c, double mp, double mm, const Half& bhat, Half
             flush(k);
             break;
         }
+        if (!ahead) next_direction();
         std::swap(cur, nxt);
         ++k;
     }
