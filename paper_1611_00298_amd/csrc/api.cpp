@@ -442,6 +442,7 @@ void run_hop(eofa_ctx* c, const HopCall& h) {
     if (h.in_p1) f *= 2, nfields *= 2;
     c->flops += f * (double)c->n5;
     double bytes = nfields * spinor_bytes(h.prec) * (double)c->n5;
+    if (h.out) bytes += (spinor_bytes(h.out->prec) - spinor_bytes(h.prec)) * (double)c->n5;   // stored in its own precision
     // algorithmic link bytes: the 4V links of one checkerboard hop, 9 complex
     // numbers each at the field precision (what the kernel reads can be more:
     // FP32 links or the FP16 rows of the matrix-core path)
