@@ -114,7 +114,10 @@ int eofa_ctx_update_gauge(eofa_ctx_t *ctx, const void *U_dev);
  *           Mhat = M_oo - M_oe M_ee^-1 M_eo of Section 5.1 (dagger: Mhat^dag);
  *           even sites of in are ignored and even sites of out are zero.
  * prec: arithmetic/storage precision of the operator (input and output
- * stay complex128).  in_dev/out_dev: 5D natural layout, may not alias. */
+ * stay complex128).  in_dev/out_dev: 5D natural layout.  The same pointer for
+ * both gives EOFA_EINVAL; fields that share memory otherwise are allowed, and
+ * in FP64 cost a copy of the input and a 5D field of workspace, which the
+ * context keeps. */
 int dwf_apply(eofa_ctx_t *ctx, double m_plus, double m_minus, int dagger, int eo,
               eofa_prec_t prec, const void *in_dev, void *out_dev);
 
@@ -230,6 +233,9 @@ int eofa_chrono(eofa_ctx_t *ctx, int depth);
  *          with dS = Re tr(G^dag dU) for any complex dU (gauge layout).
  *   chiL_dev/chiR_dev: solutions from eofa_solve; if either is NULL both
  *          are recomputed from phi_dev with `solver` (stats filled).
+ * F_dev and G_dev may share memory with chiL_dev or chiR_dev (a copy of that
+ * solution and a 5D field of workspace each, which the context keeps); they
+ * may not share memory with each other.
  * FP64 accumulation throughout. */
 int eofa_force(eofa_ctx_t *ctx, double m1, double m2, const void *phi_dev,
                const void *chiL_dev, const void *chiR_dev, void *F_dev, void *G_dev,

@@ -21,6 +21,7 @@ OBJDIR = os.path.join(HERE, "_build")
 SOURCES = ["dslash.hip", "blas.hip", "fields.hip", "force.hip", "gauge.hip", "rational.cpp", "api.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+# the kernels are laid out for gfx950 and use up to 80 KB of LDS per workgroup
 ARCH = os.environ.get("EOFA_OFFLOAD_ARCH", "gfx950")
 
 CFLAGS = [
